@@ -74,7 +74,7 @@ extern "C" {
 
 /* waves of the tiled list build (md_params.build_waves) */
 #define MD_BUILD_AUTO       0   /* a wave per tile from MD_BUILD_TILE_MIN tiles on, else a wave per cell */
-#define MD_BUILD_CELL_WAVES 1   /* a wave per cell; the cells of a tile reserve their rows by atomics   */
+#define MD_BUILD_CELL_WAVES 1   /* a wave (small grids: four) per cell; cells reserve their rows by atomics */
 #define MD_BUILD_TILE_WAVES 2   /* a wave per tile, building its cells one after another along z        */
 #define MD_BUILD_TILE_MIN   32768
 

@@ -33,11 +33,6 @@ constexpr int kLanesPerKey = MD_LANES_PER_KEY;   // lanes cooperating on one key
 constexpr int kForceUnroll = MD_FORCE_UNROLL;    // row entries in flight per lane (FP32 pair terms)
 constexpr int kForceUnroll64 = MD_FORCE_UNROLL_FP64;  // same for FP64 pair terms (register bound)
 constexpr int kKeysPerBlock = kForceBlock / kLanesPerKey;
-#ifndef MD_BUILD_NCH
-#define MD_BUILD_NCH 8
-#endif
-constexpr int kBuildChunks = MD_BUILD_NCH;   // candidates held in registers: kBuildChunks x 64
-constexpr int kBuildChunksSmall = 6;          // the same where neighbourhoods are small (fewer registers)
 constexpr int kReduceBlock = 1024;
 
 constexpr uint32_t kSlotMask = (1u << 27) - 1u;

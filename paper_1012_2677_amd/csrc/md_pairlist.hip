@@ -14,7 +14,8 @@
 // so cells never have to wait for each other (tiled lists pool the blocks of a
 // tile's cells, below).
 //
-// The work is ALU bound (about 300 FP64 distance tests per particle).
+// The work is ALU bound (about 300 FP64 distance tests per particle at
+// rho = 0.5); small grids are bound by one wave's walk over its keys.
 
 #include <cmath>
 #include <type_traits>
@@ -125,15 +126,25 @@ __device__ __forceinline__ uint32_t row_start(uint32_t end)
 #ifndef MD_BUILD_ROWBUF
 #define MD_BUILD_ROWBUF 768
 #endif
-constexpr int kRowBuf = MD_BUILD_ROWBUF;   // entries of one cell's rows staged in LDS before the block is written
+constexpr int kRowBuf = MD_BUILD_ROWBUF;
 
-template <typename E>
-__device__ __forceinline__ void pad_row(E* blk, uint32_t stride, uint32_t* s_rows, uint32_t end, uint32_t pad)
+// Words of a wave's row buffer in LDS.  The cell's buffers first hold the
+// candidate table (6 bytes per candidate).  One wave per cell (W = 1): 16-bit
+// entries with the smallest register set of candidates sized so that the
+// block's LDS stays within 5 KB (32 blocks, 8 waves per SIMD), with the
+// larger ones so that the rows of a cell of that neighbourhood usually fit.
+// Four waves per cell: a wave's quarter of the keys.
+template <int NCH, int W, typename E>
+constexpr int rowbuf_words()
 {
-    if (sizeof(E) == 2 && (end & 1u) && lane_id() == 0) {
-        if (end < (uint32_t)kRowBuf) s_rows[end] = pad;
-        else if (end < stride) blk[end] = (E)pad;
-    }
+    if (W > 1) return (NCH <= 8 ? 512 : (NCH <= 12 ? 640 : 960)) * (sizeof(E) == 2 ? 1 : 2);
+    if (sizeof(E) == 2) return NCH <= 6 ? 608 : (NCH <= 8 ? kRowBuf : (NCH <= 12 ? 1216 : 1984));
+    return NCH * 96 > kRowBuf ? NCH * 96 : kRowBuf;
+}
+template <int NCH, int W, typename E>
+constexpr uint32_t rowbuf_entries()
+{
+    return (uint32_t)(rowbuf_words<NCH, W, E>() * (4 / sizeof(E)));
 }
 
 // Keys of one cell against candidates held in registers: NACT chunks of 64
@@ -158,12 +169,12 @@ __device__ __forceinline__ void pad_row(E* blk, uint32_t stride, uint32_t* s_row
 // build, saves the select of a spare address per chunk).  The drop test is
 // one vector compare of the lane against the key's place (a scalar mask built
 // from that place would cost several scalar instructions).
-template <bool MINIMG, int NACT, bool HALF>
-__device__ __forceinline__ uint32_t row_chunks_lds(const BuildArgs& a, const double4& kp, int self_t,
-                                                   uint32_t w0, const double* cx, const double* cy,
-                                                   const double* cz, const uint32_t* meta, uint32_t* s_rows)
+template <bool MINIMG, int NACT, typename E, bool HALF>
+__device__ __forceinline__ uint32_t row_staged(const BuildArgs& a, int lane, const double4& kp, int self_t, uint32_t w0,
+                                               const double* cx, const double* cy, const double* cz,
+                                               const uint32_t* meta, E* s_rows)
 {
-    const int lane = (int)lane_id();
+    constexpr int kShift = sizeof(E) == 2 ? 1 : 2;
     uint32_t wpos = w0;
 #pragma unroll
     for (int ch = 0; ch < NACT; ++ch) {
@@ -172,20 +183,20 @@ __device__ __forceinline__ uint32_t row_chunks_lds(const BuildArgs& a, const dou
         uint64_t m = __builtin_amdgcn_ballot_w64(in);
         if (ch == 0) m &= ~__builtin_amdgcn_ballot_w64(HALF ? lane <= self_t : lane == self_t);
         if (__builtin_amdgcn_inverse_ballot_w64(m))
-            *(uint32_t*)((char*)s_rows + ((mbcnt64(m) << 2) + 4u * wpos)) = meta[ch];
+            *(E*)((char*)s_rows + ((mbcnt64(m) << kShift) + (wpos << kShift))) = (E)meta[ch];
         wpos += (uint32_t)__popcll(m);
     }
     return wpos;
 }
 
-// General form: entries go to the LDS row buffer while they fit in it, past
-// that straight to the cell block with a capacity test.
-template <bool MINIMG, int NACT, typename E, bool HALF>
-__device__ __forceinline__ uint32_t row_chunks(const BuildArgs& a, E* blk, uint32_t stride, const double4& kp,
-                                               int self_t, uint32_t w0, const double* cx, const double* cy,
-                                               const double* cz, const uint32_t* meta, uint32_t* s_rows)
+// The same row past the buffer: counted only (STORE = false), or written to
+// dst[w0 ..] where below cap (packed rows of slot entries go to the row buffer
+// lds while below room).
+template <bool MINIMG, int NACT, typename E, bool HALF, bool STORE>
+__device__ __forceinline__ uint32_t row_direct(const BuildArgs& a, int lane, const double4& kp, int self_t, uint32_t w0,
+                                               const double* cx, const double* cy, const double* cz,
+                                               const uint32_t* meta, E* dst, uint32_t cap, E* lds, uint32_t room)
 {
-    const int lane = (int)lane_id();
     uint32_t wpos = w0;
 #pragma unroll
     for (int ch = 0; ch < NACT; ++ch) {
@@ -193,83 +204,20 @@ __device__ __forceinline__ uint32_t row_chunks(const BuildArgs& a, E* blk, uint3
         const bool drop = ch == 0 && (HALF ? lane <= self_t : lane == self_t);
         const bool in = r2 < a.rs2 && !drop;
         const uint64_t m = __builtin_amdgcn_ballot_w64(in);
-        const uint32_t w = mbcnt64(m) + wpos;
-        if (in) {
-            if (w < (uint32_t)kRowBuf) s_rows[w] = meta[ch];
-            else if (w < stride) blk[w] = (E)meta[ch];
+        if (STORE) {
+            const uint32_t w = mbcnt64(m) + wpos;
+            if (in) {
+                if (lds && w < room) lds[w] = (E)meta[ch];
+                else if (w < cap) dst[w] = (E)meta[ch];
+            }
         }
         wpos += (uint32_t)__popcll(m);
     }
     return wpos;
 }
 
-template <bool MINIMG, int NACT, typename E, bool HALF>
-__device__ __forceinline__ uint32_t rows_from_registers(const BuildArgs& a, E* blk, uint32_t stride,
-                                                       int T, int own_pref, int own_cnt, const double4* s_key,
-                                                       const double* cx, const double* cy, const double* cz,
-                                                       const uint32_t* meta, uint32_t* s_rows, uint32_t* s_rowend,
-                                                       uint32_t pad)
-{
-    uint32_t used = 0;
-    for (int kk = 0; kk < own_cnt; ++kk) {
-        if (used + (uint32_t)T <= (uint32_t)kRowBuf)
-            used = row_chunks_lds<MINIMG, NACT, HALF>(a, s_key[kk], own_pref + kk, used, cx, cy, cz, meta, s_rows);
-        else
-            used = row_chunks<MINIMG, NACT, E, HALF>(a, blk, stride, s_key[kk], own_pref + kk, used, cx, cy, cz,
-                                                     meta, s_rows);
-        if (lane_id() == 0) s_rowend[kk] = used;
-        pad_row<E>(blk, stride, s_rows, used, pad);
-        used = row_start<E>(used);
-    }
-    __syncthreads();
-    // the staged part of the block, then the row headers, with full-wave stores
-    const uint32_t staged = min(min(used, (uint32_t)kRowBuf), stride);
-    if (sizeof(E) == 2) {
-        // two 16-bit entries per 32-bit store (rows start at even entries, the
-        // block base is 4-byte aligned and staged is even)
-        uint32_t* blk2 = (uint32_t*)blk;
-        for (uint32_t t = lane_id(); 2 * t < staged; t += 64) {
-            const uint2 v = *(const uint2*)(s_rows + 2 * t);
-            blk2[t] = (v.x & 0xFFFFu) | (v.y << 16);
-        }
-    } else {
-        for (uint32_t t = lane_id(); t < staged; t += 64) blk[t] = (E)s_rows[t];
-    }
-    const int kk = (int)lane_id();
-    if (kk < own_cnt) {
-        const uint32_t end = s_rowend[kk], beg = kk > 0 ? row_start<E>(s_rowend[kk - 1]) : 0u;
-        write_row(a, (int32_t)__double_as_longlong(s_key[kk].w), (int64_t)(blk - (E*)a.nbr), beg, end - beg,
-                  a.stride);
-    }
-    return used;
-}
-
-// Tiled rows.  The cells of a tile share one pooled block of tile_cells *
-// cell_stride 16-bit entries (the first cell's block and those after it): a
-// cell stages its rows in LDS as 16-bit entries, then takes its slice of the
-// pool (one atomic add, or in cell order when one wave builds the tile) and
-// writes it with full-wave 32-bit stores, so the pool has to hold the tile's
-// total rather than every cell the largest cell's rows.  With a wave per cell
-// the order of the slices inside a pool follows the order in which the cells
-// finish.  A cell whose rows outgrow the LDS buffer counts the rest,
-// takes its slice, and computes those rows again straight into it.
-
-// 16-bit entries of one tiled cell staged in LDS (the row buffer, which first
-// holds the candidate table): with the smaller register set of candidates,
-// sized so that the block's LDS stays within 5 KB (32 blocks, 8 waves per SIMD)
-template <int NCH>
-constexpr int tiled_rowbuf_words()
-{
-    return NCH <= kBuildChunksSmall ? 608 : kRowBuf;
-}
-template <int NCH>
-constexpr int rowbuf16()
-{
-    return 2 * tiled_rowbuf_words<NCH>();
-}
-
 // A cell's slice of its tile's pool: one atomic add on the tile's counter when
-// every cell has a wave of its own; when one wave builds the tile's cells one
+// every cell has waves of its own; when one wave builds the tile's cells one
 // after another (SEQ), the slices follow in cell order and the wave keeps the
 // running offset itself.
 template <bool SEQ>
@@ -281,167 +229,144 @@ __device__ __forceinline__ uint32_t reserve_slice(int lane, int32_t* tile_used, 
     return __builtin_amdgcn_readfirstlane(base);
 }
 
-template <bool MINIMG, int NACT, int NCH>
-__device__ __forceinline__ uint32_t tiled_row_lds(const BuildArgs& a, int lane, const double4& kp, int self_t,
-                                                  uint32_t w0, const double* cx, const double* cy, const double* cz,
-                                                  const uint32_t* meta, uint16_t* s_rows16)
-{
-    uint32_t wpos = w0;
-#pragma unroll
-    for (int ch = 0; ch < NACT; ++ch) {
-        const double r2 = pair_r2<MINIMG>(a, cx[ch], cy[ch], cz[ch], kp.x, kp.y, kp.z);
-        const bool in = r2 < a.rs2;
-        uint64_t m = __builtin_amdgcn_ballot_w64(in);
-        if (ch == 0) m &= ~__builtin_amdgcn_ballot_w64(lane == self_t);
-        if (__builtin_amdgcn_inverse_ballot_w64(m))
-            *(uint16_t*)((char*)s_rows16 + ((mbcnt64(m) << 1) + 2u * wpos)) = (uint16_t)meta[ch];
-        wpos += (uint32_t)__popcll(m);
-    }
-    return wpos;
-}
+// What the row makers need of one cell.
+template <typename E>
+struct CellRows {
+    int lane, wave;
+    int T, own_cnt;
+    const double4* key;      // the cell's particles, w = slot
+    E* rows;                 // this wave's row buffer
+    uint32_t* rowend;        // row ends, counted from the first row of their wave
+    uint32_t* wused;         // W > 1: entries of each wave, then the cell's slice
+    E* blk;                  // tiled: the tile's pool; slots: the cell's block
+    uint64_t cap;            // entries of it
+    int32_t* tile_used;      // tiled: entries taken in the pool
+    uint32_t seq_base;       // tiled, SEQ: the cell's slice
+    uint32_t pad;            // tiled: the stand-in that follows rows of odd length
+};
 
-// the same row, counted only (STORE = false) or written to dst[w0 ..]
-template <bool MINIMG, int NACT, bool STORE>
-__device__ __forceinline__ uint32_t tiled_row_direct(const BuildArgs& a, int lane, const double4& kp, int self_t,
-                                                     uint32_t w0, const double* cx, const double* cy,
-                                                     const double* cz, const uint32_t* meta, uint16_t* dst)
+// Rows of one cell and their headers, by W waves (wave w makes the rows of the
+// w-th part of the keys).  A wave stages its rows in LDS while they surely fit
+// (a row adds at most T - 1 entries).  With one wave, rows of slot entries past
+// the buffer go straight to the cell block.  Otherwise the rest is counted,
+// the waves' totals give each its place in the cell's slice, and the rows past
+// the buffer are computed again straight into it.  Tiled rows: the cells of a
+// tile share one pooled block of tile_cells * cell_stride 16-bit entries (the
+// first cell's block and those after it), of which a cell takes a slice once
+// its total is known, so the pool has to hold the tile's total rather than
+// every cell the largest cell's rows.  Returns the entries the cell takes.
+template <bool MINIMG, int NACT, int NCH, typename E, bool HALF, bool SEQ, int W>
+__device__ __forceinline__ uint32_t rows_from_registers(const BuildArgs& a, const CellRows<E>& r, const double* cx,
+                                                       const double* cy, const double* cz, const uint32_t* meta)
 {
-    uint32_t wpos = w0;
-#pragma unroll
-    for (int ch = 0; ch < NACT; ++ch) {
-        const double r2 = pair_r2<MINIMG>(a, cx[ch], cy[ch], cz[ch], kp.x, kp.y, kp.z);
-        const bool in = r2 < a.rs2 && (ch != 0 || lane != self_t);
-        const uint64_t m = __builtin_amdgcn_ballot_w64(in);
-        if (STORE && in) dst[mbcnt64(m) + wpos] = (uint16_t)meta[ch];
-        wpos += (uint32_t)__popcll(m);
-    }
-    return wpos;
-}
-
-// One tiled cell: rows, its slice of the tile's pool and the row headers.
-// Returns the entries the cell takes (even).
-template <bool MINIMG, int NACT, int NCH, bool SEQ>
-__device__ __forceinline__ uint32_t tiled_rows_from_registers(const BuildArgs& a, int lane, uint16_t* tblk,
-                                                             uint64_t tcap, int32_t* tile_used, uint32_t seq_base,
-                                                             int T, int own_pref, int own_cnt, const double4* s_key,
-                                                             const double* cx, const double* cy, const double* cz,
-                                                             const uint32_t* meta, uint16_t* s_rows16,
-                                                             uint32_t* s_rowend, uint32_t pad)
-{
+    constexpr bool TILED = sizeof(E) == 2;
+    constexpr uint32_t ROOM = rowbuf_entries<NCH, W, E>();
+    const int lane = r.lane;
+    const int per = W > 1 ? (r.own_cnt + W - 1) / W : r.own_cnt;
+    const int k0 = W > 1 ? min(r.wave * per, r.own_cnt) : 0, k1 = min(k0 + per, r.own_cnt);
     uint32_t used = 0;
-    int kk = 0;
-    // rows staged while they surely fit: a row adds at most T - 1 entries
-    for (; kk < own_cnt && used + (uint32_t)T <= (uint32_t)rowbuf16<NCH>(); ++kk) {
-        used = tiled_row_lds<MINIMG, NACT, NCH>(a, lane, s_key[kk], own_pref + kk, used, cx, cy, cz, meta, s_rows16);
+    int kk = k0;
+    for (; kk < k1 && used + (uint32_t)r.T <= ROOM; ++kk) {
+        used = row_staged<MINIMG, NACT, E, HALF>(a, lane, r.key[kk], kk, used, cx, cy, cz, meta, r.rows);
         if (lane == 0) {
-            s_rowend[kk] = used;
-            if (used & 1u) s_rows16[used] = (uint16_t)pad;
+            r.rowend[kk] = used;
+            if (TILED && (used & 1u)) r.rows[used] = (E)r.pad;
         }
-        used = (used + 1u) & ~1u;
+        used = row_start<E>(used);
     }
     const int ks = kk;
-    const uint32_t staged = used;
-    // the rest counted, then computed again into the slice below
-    for (int k2 = ks; k2 < own_cnt; ++k2) {
-        used = tiled_row_direct<MINIMG, NACT, false>(a, lane, s_key[k2], own_pref + k2, used, cx, cy, cz, meta, nullptr);
-        if (lane == 0) s_rowend[k2] = used;
-        used = (used + 1u) & ~1u;
+    uint32_t staged = used;
+    constexpr bool PACKED = !TILED && W == 1;
+    for (; kk < k1; ++kk) {
+        used = row_direct<MINIMG, NACT, E, HALF, PACKED>(a, lane, r.key[kk], kk, used, cx, cy, cz, meta, r.blk,
+                                                         (uint32_t)r.cap, r.rows, ROOM);
+        if (lane == 0) r.rowend[kk] = used;
+        used = row_start<E>(used);
     }
-    const uint32_t base = reserve_slice<SEQ>(lane, tile_used, seq_base, used);
-    const bool fits = (uint64_t)base + used <= tcap;
-    if (!fits && lane == 0) atomicOr((unsigned long long*)&a.status[2], 1ull);
-    __syncthreads();
-    uint16_t* dst = tblk + base;
-    if (fits) {
-        // base and staged are even and the pool starts 4-byte aligned
-        uint32_t* dst2 = (uint32_t*)dst;
-        const uint32_t* src2 = (const uint32_t*)s_rows16;
-        for (uint32_t t = lane; 2 * t < staged; t += 64) dst2[t] = src2[t];
+    uint32_t total = used, first = 0, base = 0;
+    if constexpr (W > 1) {
+        if (lane == 0) r.wused[r.wave] = used;
+        __syncthreads();
+        total = 0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const uint32_t u = r.wused[w];
+            if (w < r.wave) first += u;
+            total += u;
+        }
+        if constexpr (TILED) {
+            if (r.wave == 0) base = reserve_slice<false>(lane, r.tile_used, 0u, total);
+            if (threadIdx.x == 0) r.wused[W] = base;
+            __syncthreads();
+            base = r.wused[W];
+        }
+    } else if constexpr (TILED) {
+        base = reserve_slice<SEQ>(lane, r.tile_used, r.seq_base, used);
+        __syncthreads();
+    } else {
+        staged = min(used, ROOM);
+        __syncthreads();
+    }
+    const bool fits = (uint64_t)base + total <= r.cap;
+    if (TILED && !fits && threadIdx.x == 0) atomicOr((unsigned long long*)&a.status[2], 1ull);
+    E* dst = r.blk + base + first;
+    const uint32_t room = fits ? total - first : (uint32_t)(r.cap > first ? r.cap - first : 0);   // slots: clipped
+    if constexpr (TILED) {
+        if (fits) {
+            // base, first and staged are even and the pool starts 4-byte aligned
+            uint32_t* dst2 = (uint32_t*)dst;
+            const uint32_t* src2 = (const uint32_t*)r.rows;
+            for (uint32_t t = lane; 2 * t < staged; t += 64) dst2[t] = src2[t];
+        }
+    } else {
+        for (uint32_t t = lane; t < min(staged, room); t += 64) dst[t] = r.rows[t];
+    }
+    if (!PACKED && (!TILED || fits)) {
         uint32_t w = staged;
-        for (int k2 = ks; k2 < own_cnt; ++k2) {
-            w = tiled_row_direct<MINIMG, NACT, true>(a, lane, s_key[k2], own_pref + k2, w, cx, cy, cz, meta, dst);
-            if (lane == 0 && (w & 1u)) dst[w] = (uint16_t)pad;
-            w = (w + 1u) & ~1u;
+        for (int k2 = ks; k2 < k1; ++k2) {
+            w = row_direct<MINIMG, NACT, E, HALF, true>(a, lane, r.key[k2], k2, w, cx, cy, cz, meta, dst, room, nullptr,
+                                                        0u);
+            if (TILED && lane == 0 && (w & 1u)) dst[w] = (E)r.pad;
+            w = row_start<E>(w);
         }
     }
-    if (lane < own_cnt) {
-        const uint32_t end = s_rowend[lane], beg = lane > 0 ? (s_rowend[lane - 1] + 1u) & ~1u : 0u;
-        const int32_t kslot = (int32_t)__double_as_longlong(s_key[lane].w);
-        // an overflowed cell (list invalid) keeps in-range, empty rows
-        a.offsets[kslot] = (int64_t)((fits ? dst : tblk) - (uint16_t*)a.nbr) + (fits ? beg : 0u);
-        a.counts[kslot] = fits ? (int32_t)(end - beg) : 0;
+    if (k0 + lane < k1) {
+        const int k2 = k0 + lane;
+        const uint32_t end = r.rowend[k2], beg = lane > 0 ? row_start<E>(r.rowend[k2 - 1]) : 0u;
+        const int32_t kslot = (int32_t)__double_as_longlong(r.key[k2].w);
+        if constexpr (TILED) {
+            // an overflowed cell (list invalid) keeps in-range, empty rows
+            a.offsets[kslot] = (int64_t)((fits ? dst : r.blk) - (E*)a.nbr) + (fits ? beg : 0u);
+            a.counts[kslot] = fits ? (int32_t)(end - beg) : 0;
+        } else {
+            write_row(a, kslot, (int64_t)(r.blk - (E*)a.nbr), first + beg, end - beg, (int64_t)r.cap);
+        }
     }
-    return used;
+    return total;
 }
 
-template <bool MINIMG, int NCH, bool SEQ>
-__device__ __forceinline__ uint32_t tiled_rows_for_chunks(int nact, const BuildArgs& a, int lane, uint16_t* tblk,
-                                                         uint64_t tcap, int32_t* tile_used, uint32_t seq_base, int T,
-                                                         int own_pref, int own_cnt, const double4* s_key,
-                                                         const double* cx, const double* cy, const double* cz,
-                                                         const uint32_t* meta, uint16_t* s_rows16, uint32_t* s_rowend,
-                                                         uint32_t pad)
+// The key loop for the cell's chunk count nact in [1, NCH], instantiated for
+// the chunk counts LOW, LOW + STEP, ... and NCH (the counts that the register
+// set's neighbourhoods usually have; chunks past T hold no candidate).
+template <int LOW, int STEP, bool MINIMG, int NCH, typename E, bool HALF, bool SEQ, int W>
+__device__ __forceinline__ uint32_t rows_for_chunks(int nact, const BuildArgs& a, const CellRows<E>& r,
+                                                   const double* cx, const double* cy, const double* cz,
+                                                   const uint32_t* meta)
 {
-    static_assert(NCH >= 2 && NCH <= 8, "one case per chunk count");
-#define MD_TROWS_CASE(N)                                                                                              \
-    case N:                                                                                                           \
-        if constexpr (N < NCH)                                                                                        \
-            return tiled_rows_from_registers<MINIMG, N, NCH, SEQ>(a, lane, tblk, tcap, tile_used, seq_base, T, own_pref,  \
-                                                             own_cnt, s_key, cx, cy, cz, meta, s_rows16, s_rowend, pad); \
-        break;
-    switch (nact) {
-        MD_TROWS_CASE(1)
-        MD_TROWS_CASE(2)
-        MD_TROWS_CASE(3)
-        MD_TROWS_CASE(4)
-        MD_TROWS_CASE(5)
-        MD_TROWS_CASE(6)
-        MD_TROWS_CASE(7)
-        default:
-            break;
+    if constexpr (LOW < NCH) {
+        if (nact <= LOW) return rows_from_registers<MINIMG, LOW, NCH, E, HALF, SEQ, W>(a, r, cx, cy, cz, meta);
+        return rows_for_chunks<LOW + STEP, STEP, MINIMG, NCH, E, HALF, SEQ, W>(nact, a, r, cx, cy, cz, meta);
+    } else {
+        return rows_from_registers<MINIMG, NCH, NCH, E, HALF, SEQ, W>(a, r, cx, cy, cz, meta);
     }
-#undef MD_TROWS_CASE
-    return tiled_rows_from_registers<MINIMG, NCH, NCH, SEQ>(a, lane, tblk, tcap, tile_used, seq_base, T, own_pref, own_cnt, s_key,
-                                                       cx, cy, cz, meta, s_rows16, s_rowend, pad);
 }
 
-// The key loop for the cell's chunk count nact in [1, NCH].
-template <bool MINIMG, int NCH, typename E, bool HALF>
-__device__ __forceinline__ uint32_t rows_for_chunks(int nact, const BuildArgs& a, E* blk, uint32_t stride, int T,
-                                                   int own_pref, int own_cnt, const double4* s_key, const double* cx,
-                                                   const double* cy, const double* cz, const uint32_t* meta,
-                                                   uint32_t* s_rows, uint32_t* s_rowend, uint32_t pad)
-{
-    static_assert(NCH >= 2 && NCH <= 8, "one case per chunk count");
-#define MD_ROWS_CASE(N)                                                                                             \
-    case N:                                                                                                         \
-        if constexpr (N < NCH)                                                                                      \
-            return rows_from_registers<MINIMG, N, E, HALF>(a, blk, stride, T, own_pref, own_cnt, s_key, cx, cy, cz, \
-                                                            meta, s_rows, s_rowend, pad);                           \
-        break;
-    switch (nact) {
-        MD_ROWS_CASE(1)
-        MD_ROWS_CASE(2)
-        MD_ROWS_CASE(3)
-        MD_ROWS_CASE(4)
-        MD_ROWS_CASE(5)
-        MD_ROWS_CASE(6)
-        MD_ROWS_CASE(7)
-        default:
-            break;
-    }
-#undef MD_ROWS_CASE
-    return rows_from_registers<MINIMG, NCH, E, HALF>(a, blk, stride, T, own_pref, own_cnt, s_key, cx, cy, cz, meta,
-                                                     s_rows, s_rowend, pad);
-}
-
-// Same rows, candidates re-read from memory for every key (neighbourhoods with
-// more than NCH*64 particles or cells with more than 64 particles: never at
-// liquid densities, kept for generality).
+// Same rows, by one wave, candidates re-read from memory for every key
+// (neighbourhoods with more than NCH*64 particles or cells with more than 64).
 // COUNT: only the rows' total (with the even starts of 16-bit rows) is
 // returned, nothing is written.
 template <bool MINIMG, typename E, bool HALF, bool COUNT = false>
-__device__ uint32_t rows_from_memory(const BuildArgs& a, E* blk, uint32_t stride, int T, int own_start,
+__device__ __forceinline__ uint32_t rows_from_memory(const BuildArgs& a, E* blk, uint32_t stride, int T, int own_start,
                                      int own_cnt, const int* s_pref, const int* s_nstart, const int* s_lbase,
                                      uint32_t pad)
 {
@@ -457,7 +382,9 @@ __device__ uint32_t rows_from_memory(const BuildArgs& a, E* blk, uint32_t stride
             uint32_t meta = 0;
             if (t < T) {
                 int q = 0;
-                while (s_pref[q + 1] <= t) ++q;
+#pragma unroll
+                for (int h = 16; h > 0; h >>= 1)
+                    if (q + h < 27 && s_pref[q + h] <= t) q += h;
                 const int idx = s_nstart[q] + (t - s_pref[q]);
                 const int32_t slot = a.order ? a.order[idx] : idx;
                 const double4 p = a.pos[slot];
@@ -529,7 +456,7 @@ __device__ __forceinline__ TileCtx tile_ctx(const BuildArgs& a, int cx, int cy, 
 // neighbour cells (lane q < 27 holds those of cell q; half rows use q >= 13
 // only).  Tiled: the cell's slice of the tile's pool is reserved by an atomic
 // add or, SEQ, starts at seq_base.  Returns the entries the cell takes.
-template <int NCH, bool TILED, bool HALF, bool SEQ>
+template <int NCH, bool TILED, bool HALF, bool SEQ, int W>
 __device__ __forceinline__ uint32_t build_cell(const BuildArgs& a, int cx, int cy, int cz, int st_l, int cnt_l,
                                                const TileCtx& tx, uint32_t seq_base)
 {
@@ -539,17 +466,19 @@ __device__ __forceinline__ uint32_t build_cell(const BuildArgs& a, int cx, int c
     // addresses below are then formed per cell instead of being hoisted out of
     // the cell loop into registers that stay live across it
     if (SEQ) asm volatile("" : "+v"(lane));
+    const int wave = W > 1 ? (int)(threadIdx.x >> 6) : 0;
     const int nx = a.nc[0], ny = a.nc[1], nz = a.nc[2];
     const int64_t c = ((int64_t)cx * ny + cy) * nz + cz;
 
     __shared__ int s_nstart[27];
     __shared__ int s_pref[28];
     __shared__ double4 s_key[kMaxOwn];
-    // rows of the cell's keys before the block is written (and two words of
+    // rows of the waves' keys before the block is written (and two words of
     // margin); before that, the candidate table
-    constexpr int kRows = TILED ? tiled_rowbuf_words<NCH>() : kRowBuf;
-    __shared__ __align__(8) uint32_t s_rows[kRows + 2];
+    constexpr int kRows = rowbuf_words<NCH, W, E>();
+    __shared__ __align__(8) uint32_t s_rows[W * kRows + 2];
     __shared__ uint32_t s_rowend[kMaxOwn];
+    __shared__ uint32_t s_wused[W + 1];
     __shared__ int s_lbase[27];
     const bool has_nb = lane < 27 && (!HALF || lane <= 13);
     const int st = has_nb ? st_l : 0, cnt = has_nb ? cnt_l : 0;
@@ -569,9 +498,8 @@ __device__ __forceinline__ uint32_t build_cell(const BuildArgs& a, int cx, int c
 
     const int T = s_pref[27];
     const uint32_t pad = TILED ? tx.pad : 0u;
-    const int own_pref = 0;   // the own cell's particles are the first candidates
     const int own_start = s_nstart[0];
-    const int own_cnt = s_pref[1];
+    const int own_cnt = s_pref[1];   // the own cell's particles are the first candidates
     const bool minimg = a.exact_all || cx == 0 || cx == nx - 1 || cy == 0 || cy == ny - 1 || cz == 0 ||
                         cz == nz - 1;
     E* blk = (E*)a.nbr + c * a.stride;
@@ -584,18 +512,18 @@ __device__ __forceinline__ uint32_t build_cell(const BuildArgs& a, int cx, int c
         // order and (16 bits) its staged index in the tile's neighbourhood
         // (tiled) or its stencil code, written by the lane of its cell; it
         // lives in the row buffer, which is free until the rows are made
-        static_assert(NCH * 64 * (sizeof(uint32_t) + sizeof(uint16_t)) <= sizeof(uint32_t) * (kRows + 2),
+        static_assert(NCH * 64 * (sizeof(uint32_t) + sizeof(uint16_t)) <= sizeof(uint32_t) * (W * kRows + 2),
                       "table fits the row buffer");
         uint32_t* s_tpos = s_rows;
         uint16_t* s_tcode = reinterpret_cast<uint16_t*>(s_rows + NCH * 64);
-        // two lanes per neighbour cell (lanes q and q + 32 for q < 27), each
-        // writing every other entry of it
+        // two lanes of each wave per neighbour cell (lanes q and q + 32 for
+        // q < 27), each writing every other entry of the wave's share of it
         {
             const int q = lane & 31;
             const int t0 = __shfl(incl - cnt, q, 64), stq = __shfl(st, q, 64), cq = __shfl(cnt, q, 64);
             const int eq = TILED ? __shfl(lb, q, 64) : code_of_rank(q);
             if (q < 27) {
-                for (int i = lane >> 5; i < cq; i += 2) {
+                for (int i = (lane >> 5) + 2 * wave; i < cq; i += 2 * W) {
                     s_tpos[t0 + i] = (uint32_t)(stq + i);
                     s_tcode[t0 + i] = (uint16_t)(TILED ? eq + i : eq);
                 }
@@ -625,21 +553,28 @@ __device__ __forceinline__ uint32_t build_cell(const BuildArgs& a, int cx, int c
         }
         __syncthreads();
         const int nact = (T + 63) >> 6;
-        if constexpr (TILED) {
-            uint16_t* s_rows16 = reinterpret_cast<uint16_t*>(s_rows);
-            used = minimg ? tiled_rows_for_chunks<true, NCH, SEQ>(nact, a, lane, tx.tblk, tx.tcap, tx.tused, seq_base, T,
-                                                                  own_pref, own_cnt, s_key, px, py, pz, meta,
-                                                                  s_rows16, s_rowend, pad)
-                          : tiled_rows_for_chunks<false, NCH, SEQ>(nact, a, lane, tx.tblk, tx.tcap, tx.tused, seq_base, T,
-                                                                   own_pref, own_cnt, s_key, px, py, pz, meta,
-                                                                   s_rows16, s_rowend, pad);
-        } else {
-            used = minimg ? rows_for_chunks<true, NCH, E, HALF>(nact, a, blk, stride, T, own_pref, own_cnt, s_key,
-                                                                px, py, pz, meta, s_rows, s_rowend, pad)
-                          : rows_for_chunks<false, NCH, E, HALF>(nact, a, blk, stride, T, own_pref, own_cnt, s_key,
-                                                                 px, py, pz, meta, s_rows, s_rowend, pad);
-        }
-    } else if (own_cnt > 0) {
+        CellRows<E> r;
+        r.lane = lane;
+        r.wave = wave;
+        r.T = T;
+        r.own_cnt = own_cnt;
+        r.key = s_key;
+        r.rows = reinterpret_cast<E*>(s_rows + wave * kRows);
+        r.rowend = s_rowend;
+        r.wused = s_wused;
+        r.blk = TILED ? (E*)tx.tblk : blk;
+        r.cap = TILED ? tx.tcap : (uint64_t)stride;
+        r.tile_used = tx.tused;
+        r.seq_base = seq_base;
+        r.pad = pad;
+        // four waves per cell (small grids, most of whose cells touch the box
+        // faces) always take minimum images, which change nothing elsewhere
+        constexpr int LOW = NCH <= 6 ? 1 : (NCH <= 8 ? (W > 1 ? 4 : 1) : (NCH <= 12 ? 8 : 14)), STEP = NCH <= 12 ? 1 : 2;
+        if (W > 1 || minimg)
+            used = rows_for_chunks<LOW, STEP, true, NCH, E, HALF, SEQ, W>(nact, a, r, px, py, pz, meta);
+        else
+            used = rows_for_chunks<LOW, STEP, W == 1 ? false : true, NCH, E, HALF, SEQ, W>(nact, a, r, px, py, pz, meta);
+    } else if (own_cnt > 0 && wave == 0) {
         if constexpr (TILED) {
             // count the rows, take the cell's slice of the tile's pool, write
             const uint32_t total =
@@ -665,25 +600,26 @@ __device__ __forceinline__ uint32_t build_cell(const BuildArgs& a, int cx, int c
                                                              s_nstart, nullptr, pad);
         }
     }
-    if (lane == 0) {
+    if (lane == 0 && wave == 0) {
         a.cell_rows[c] = used > 0x7FFFFFFFu ? 0x7FFFFFFF : (int32_t)used;
         if (!TILED && used > stride) atomicOr((unsigned long long*)&a.status[2], 1ull);
     }
     return used;
 }
 
-// One wave per cell, or (SEQ, tiled lists of large grids) one wave per tile
+// One wave per cell (four on small grids, whose cells alone would leave most of
+// the GPU idle while each wave walks its cell's keys), or (SEQ, tiled lists of large grids) one wave per tile
 // that builds the tile's cells one after another along z: the cells' slices
 // of the tile's pool then follow in cell order with no atomic, the tile's runs
 // and staged layout are worked out once, and the next cell's neighbour starts
 // and counts load while a cell is built.
-template <int NCH, bool TILED, bool HALF, bool SEQ>
-__global__ __launch_bounds__(64) void k_build(BuildArgs a)
+template <int NCH, bool TILED, bool HALF, bool SEQ, int W>
+__global__ __launch_bounds__(64 * W) void k_build(BuildArgs a)
 {
-    static_assert(!SEQ || (TILED && !HALF), "tile-sequential builds write tiled full rows");
+    static_assert(!SEQ || (TILED && !HALF && W == 1), "tile-sequential builds write tiled full rows");
     const int64_t tb = xcd_remap(blockIdx.x, gridDim.x);
     if (tb >= (SEQ ? a.ntile : a.ncell)) return;
-    const int lane = (int)threadIdx.x;
+    const int lane = (int)(threadIdx.x & 63);
     const int nx = a.nc[0], ny = a.nc[1], nz = a.nc[2];
     // cells (tiles) in strips of kBuildStrip x-columns walked along y (a
     // column's cells consecutive), so that cells built close in time share
@@ -726,11 +662,11 @@ __global__ __launch_bounds__(64) void k_build(BuildArgs a)
     TileCtx tx;
     if (TILED) {
         tx = tile_ctx(a, cx, cy, tz, z0, z1, run);
-        if (lane == 0 && cz0 == z0)
+        if (threadIdx.x == 0 && cz0 == z0)
             atomicMax(a.tile_max + (tx.tile & (kTileMaxSlots - 1)), (unsigned long long)tx.total);
     }
     if constexpr (!SEQ) {
-        build_cell<NCH, TILED, HALF, false>(a, cx, cy, cz0, st_l, cnt_l, tx, 0u);
+        build_cell<NCH, TILED, HALF, false, W>(a, cx, cy, cz0, st_l, cnt_l, tx, 0u);
     } else {
         uint32_t off = 0;
         for (int cz = z0; cz < z1; ++cz) {
@@ -742,7 +678,7 @@ __global__ __launch_bounds__(64) void k_build(BuildArgs a)
                 st_n = a.start[nbn];
                 cnt_n = a.count[nbn];
             }
-            off += build_cell<NCH, true, false, true>(a, cx, cy, cz, st_l, cnt_l, tx, off);
+            off += build_cell<NCH, true, false, true, 1>(a, cx, cy, cz, st_l, cnt_l, tx, off);
             st_l = st_n;
             cnt_l = cnt_n;
             __syncthreads();
@@ -784,6 +720,15 @@ __global__ __launch_bounds__(256) void k_tile_need_final(const int32_t* __restri
     if (threadIdx.x == 0) status[1] = m;
 }
 
+// Four waves per cell up to this many cells.  Time of a rebuild's list (build
+// and statistics, us, one / four waves per cell): 343 cells at 12 particles
+// each 31.0 / 25.5, 343 at 32 each 49.8 / 32.4, 64 at 32 each 69.7 / 37.8;
+// 2744 cells at 12 each 36.3 / 39.2, 3375 at 19 each 56.4 / 63.7: beyond about
+// a thousand the cells' own waves fill the SIMDs, and four times the candidate
+// loads cost more than the shorter key walks save.
+constexpr int64_t kWideCells = 1024;
+
+
 hipError_t launch_build(const Geo& g, double rs, const double* pos, const md_cells& cells,
                         const md_pairlist& list, void* ws, const WsLayout& L, bool tiled, bool half,
                         unsigned long long* tile_max, int waves, hipStream_t s)
@@ -818,36 +763,57 @@ hipError_t launch_build(const Geo& g, double rs, const double* pos, const md_cel
     a.ntile = g.ntile;
     a.div_nt = make_fastdiv((uint32_t)(g.nt > 0 ? g.nt : 1));
     if (tiled && (half || !cells.sorted || g.tc <= 0 || !tile_max)) return hipErrorInvalidValue;
+    // candidates held in registers: the fewest chunks of 64 (fewer registers,
+    // more waves per SIMD) that a neighbourhood far in the tail at the mean
+    // density needs (4 standard deviations of a Poisson count above the mean,
+    // 2 where that takes a larger set than 8 chunks: a liquid dense enough for
+    // it fluctuates far less); larger neighbourhoods take the path that
+    // re-reads memory for every key (11k particles at density 0.8, 690
+    // candidates per cell: 600 us per build on that path, 50 with the set of
+    // 12 chunks and one wave per cell; 256k at 0.8: 526 and 113 us; 1M at 0.8,
+    // 477 candidates: 303 us with 8 chunks and the few larger cells on that
+    // path, 520 with 12 chunks for all)
+    const double mean_t = (half ? 14.0 : 27.0) * (double)g.n / (double)g.ncell, dev_t = std::sqrt(mean_t);
+    const double most4 = mean_t + 4.0 * dev_t, most2 = mean_t + 2.0 * dev_t;
+    const int nch = most4 <= 384.0 ? 6 : (most2 <= 512.0 ? 8 : (most2 <= 768.0 ? 12 : 20));
     // one wave per tile where the tiles alone fill the GPU several times over
-    // (below that, the cells' own waves keep more of it busy)
-    const bool seq =
-        tiled && (waves == MD_BUILD_TILE_WAVES || (waves == MD_BUILD_AUTO && g.ntile >= MD_BUILD_TILE_MIN));
+    // (below that, the cells' own waves keep more of it busy), and with the
+    // smaller register sets
+    const bool seq = tiled && (waves == MD_BUILD_TILE_WAVES ||
+                               (waves == MD_BUILD_AUTO && g.ntile >= MD_BUILD_TILE_MIN && nch <= 8));
     // status[2] (overflow) is cleared by the statistics kernel of the previous
     // build or by the caller; clear it here on the stream before the build.
     hipError_t e = launch_fill_i32((int32_t*)list.status, 0, 8, s);
     if (e != hipSuccess) return e;
     if (tiled && !seq && (e = launch_fill_i32(tile_used, 0, g.ntile, s)) != hipSuccess) return e;
     const dim3 grid((unsigned)(seq ? g.ntile : g.ncell));
-    // candidates held in registers: 6 chunks of 64 (fewer registers, more
-    // waves per SIMD) when a neighbourhood that large is far in the tail at
-    // the mean density (4 standard deviations of a Poisson count above the
-    // mean), else 8; larger neighbourhoods take the path that re-reads
-    // memory for every key
-    const double mean_t = (half ? 14.0 : 27.0) * (double)g.n / (double)g.ncell;
-    const bool small = mean_t + 4.0 * std::sqrt(mean_t) <= (double)(kBuildChunksSmall * 64);
+    const bool wide = !seq && !half && g.ncell <= kWideCells;
+#define MD_BUILD_LAUNCH(N, TILED, HALF, SEQ, W) \
+    hipLaunchKernelGGL((k_build<N, TILED, HALF, SEQ, W>), grid, dim3(64 * W), 0, s, a)
     if (seq) {
-        if (small) hipLaunchKernelGGL((k_build<kBuildChunksSmall, true, false, true>), grid, dim3(64), 0, s, a);
-        else hipLaunchKernelGGL((k_build<kBuildChunks, true, false, true>), grid, dim3(64), 0, s, a);
-    } else if (tiled) {
-        if (small) hipLaunchKernelGGL((k_build<kBuildChunksSmall, true, false, false>), grid, dim3(64), 0, s, a);
-        else hipLaunchKernelGGL((k_build<kBuildChunks, true, false, false>), grid, dim3(64), 0, s, a);
+        if (nch == 6) MD_BUILD_LAUNCH(6, true, false, true, 1);
+        else MD_BUILD_LAUNCH(8, true, false, true, 1);
     } else if (half) {
-        if (small) hipLaunchKernelGGL((k_build<kBuildChunksSmall, false, true, false>), grid, dim3(64), 0, s, a);
-        else hipLaunchKernelGGL((k_build<kBuildChunks, false, true, false>), grid, dim3(64), 0, s, a);
+        if (nch == 6) MD_BUILD_LAUNCH(6, false, true, false, 1);
+        else MD_BUILD_LAUNCH(8, false, true, false, 1);
+    } else if (tiled) {
+        if (wide && nch <= 8) MD_BUILD_LAUNCH(8, true, false, false, 4);
+        else if (wide && nch == 12) MD_BUILD_LAUNCH(12, true, false, false, 4);
+        else if (wide) MD_BUILD_LAUNCH(20, true, false, false, 4);
+        else if (nch == 6) MD_BUILD_LAUNCH(6, true, false, false, 1);
+        else if (nch == 8) MD_BUILD_LAUNCH(8, true, false, false, 1);
+        else if (nch == 12) MD_BUILD_LAUNCH(12, true, false, false, 1);
+        else MD_BUILD_LAUNCH(20, true, false, false, 1);
     } else {
-        if (small) hipLaunchKernelGGL((k_build<kBuildChunksSmall, false, false, false>), grid, dim3(64), 0, s, a);
-        else hipLaunchKernelGGL((k_build<kBuildChunks, false, false, false>), grid, dim3(64), 0, s, a);
+        if (wide && nch <= 8) MD_BUILD_LAUNCH(8, false, false, false, 4);
+        else if (wide && nch == 12) MD_BUILD_LAUNCH(12, false, false, false, 4);
+        else if (wide) MD_BUILD_LAUNCH(20, false, false, false, 4);
+        else if (nch == 6) MD_BUILD_LAUNCH(6, false, false, false, 1);
+        else if (nch == 8) MD_BUILD_LAUNCH(8, false, false, false, 1);
+        else if (nch == 12) MD_BUILD_LAUNCH(12, false, false, false, 1);
+        else MD_BUILD_LAUNCH(20, false, false, false, 1);
     }
+#undef MD_BUILD_LAUNCH
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     e = launch_list_stats(a.cell_rows, g.ncell, list.status, (long long*)((char*)ws + L.red), s);
