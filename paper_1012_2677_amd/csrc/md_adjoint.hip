@@ -21,6 +21,7 @@ namespace md {
 struct AdjArgs {
     const double4* pos;
     const int32_t* cell_xyz;
+    const int32_t* order;        // slots in cell order (nullptr: they are in it)
     const int64_t* offsets;
     const int32_t* counts;
     const uint32_t* nbr;
@@ -82,9 +83,12 @@ template <int G, int U, bool HAS_U>
 __global__ __launch_bounds__(kForceBlock) void k_adjoint(AdjArgs a)
 {
     const int64_t blk = xcd_remap(blockIdx.x, gridDim.x);
-    const int64_t key = blk * (kForceBlock / G) + threadIdx.x / G;
+    const int64_t place = blk * (kForceBlock / G) + threadIdx.x / G;
     const int sub = threadIdx.x % G;
-    const bool valid = key < a.n;
+    const bool valid = place < a.n;
+    // keys in cell order, so that those walked together share their partners
+    // in the caches
+    const int64_t key = valid && a.order ? a.order[place] : place;
     const int64_t n = a.n;
     int64_t off = 0;
     int cnt = 0;
@@ -205,12 +209,13 @@ __global__ __launch_bounds__(kForceBlock) void k_adjoint(AdjArgs a)
 #endif
 constexpr int kAdjUnroll = MD_ADJ_UNROLL;   // row entries in flight per lane
 
-static AdjArgs make_args(const Geo& g, const LJ& lj, const double* pos, const int32_t* cell_xyz,
+static AdjArgs make_args(const Geo& g, const LJ& lj, const double* pos, const md_cells& cells,
                          const md_pairlist& list)
 {
     AdjArgs a;
     a.pos = (const double4*)pos;
-    a.cell_xyz = cell_xyz;
+    a.cell_xyz = cells.cell_xyz;
+    a.order = cells.sorted ? nullptr : cells.order;
     a.offsets = list.offsets;
     a.counts = list.counts;
     a.nbr = list.nbr;
@@ -241,10 +246,10 @@ static void launch_adj(const Geo& g, const AdjArgs& a, hipStream_t s)
         hipLaunchKernelGGL((k_adjoint<kLanesPerKey, kAdjUnroll, false>), grid, block, 0, s, a);
 }
 
-hipError_t launch_hvp(const Geo& g, const LJ& lj, const double* pos, const int32_t* cell_xyz,
+hipError_t launch_hvp(const Geo& g, const LJ& lj, const double* pos, const md_cells& cells,
                       const md_pairlist& list, const double* u, double* Hu, double* part, hipStream_t s)
 {
-    AdjArgs a = make_args(g, lj, pos, cell_xyz, list);
+    AdjArgs a = make_args(g, lj, pos, cells, list);
     a.u = u;
     a.out = Hu;
     a.beta = 1.0;
@@ -254,21 +259,21 @@ hipError_t launch_hvp(const Geo& g, const LJ& lj, const double* pos, const int32
     return hipGetLastError();
 }
 
-hipError_t launch_param_grad(const Geo& g, const LJ& lj, const double* pos, const int32_t* cell_xyz,
+hipError_t launch_param_grad(const Geo& g, const LJ& lj, const double* pos, const md_cells& cells,
                              const md_pairlist& list, double* part, hipStream_t s)
 {
-    AdjArgs a = make_args(g, lj, pos, cell_xyz, list);
+    AdjArgs a = make_args(g, lj, pos, cells, list);
     a.part = part;
     a.cU = 1.0;
     launch_adj(g, a, s);
     return hipGetLastError();
 }
 
-hipError_t launch_adjoint_kick(const Geo& g, const LJ& lj, const double* pos, const int32_t* cell_xyz,
+hipError_t launch_adjoint_kick(const Geo& g, const LJ& lj, const double* pos, const md_cells& cells,
                                const md_pairlist& list, const double* u, double* out, double* u_out,
                                const AdjCoef& k, double* part, hipStream_t s)
 {
-    AdjArgs a = make_args(g, lj, pos, cell_xyz, list);
+    AdjArgs a = make_args(g, lj, pos, cells, list);
     a.u = u;
     a.out = out;
     a.u_out = u_out;

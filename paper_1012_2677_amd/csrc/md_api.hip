@@ -144,7 +144,7 @@ WsLayout ws_layout(const Geo& g, int64_t ldc_max, int precision)
     WsLayout L;
     L.nbs = ceil_div(ncell, kScanItems);
     L.nbf = ceil_div(n, kKeysPerBlock);
-    const int64_t np = std::max(pair_blocks(g), g.ntile);
+    const int64_t np = std::max(pair_blocks(g), g.ntile);   // (a half list's pass has at most as many)
     L.nbi = ceil_div(n, kStreamBlock);
     size_t off = 0;
     L.rank = off;      off = align256(off + sizeof(int32_t) * (size_t)n);
@@ -389,10 +389,12 @@ static int forces_with(const Ctx& c, const md_params* p, const double* pos, cons
     out.force = force;
     out.part = pe_w ? part : nullptr;
     out.flags = flags;
-    MD_HIP(launch_forces(c.g, c.lj, p->precision, pos, pos32, cells->cell_xyz, *list, out, stream),
+    TileIo keys;
+    keys.order = cells->sorted ? nullptr : cells->order;
+    MD_HIP(launch_forces(c.g, c.lj, p->precision, pos, pos32, cells->cell_xyz, *list, out, stream, keys),
            "md_forces");
     if (pe_w)
-        MD_HIP(launch_reduce_pair(out.part, force_blocks(c.g, false), 1.0, 1.0, pe_w, stream), "md_forces/reduce");
+        MD_HIP(launch_reduce_pair(out.part, force_blocks(c.g, false, list->half != 0), 1.0, 1.0, pe_w, stream), "md_forces/reduce");
     return MD_OK;
 }
 
@@ -419,6 +421,7 @@ int md_forces(const md_params* p, const double* pos, const md_cells* cells, cons
 // ---------------------------------------------------------------------------
 constexpr int64_t kNoAllocMaxN = MD_NOALLOC_MAX_N;
 constexpr size_t kNoAllocPos32 = 16 * (size_t)kNoAllocMaxN;
+// (pair_blocks is largest at the most particles: a chunk per kForceBlock of them)
 constexpr size_t kNoAllocPart = sizeof(double) * 2 * (size_t)((kNoAllocMaxN + kForceBlock - 1) / kForceBlock);
 constexpr size_t kNoAllocFlags = 256;
 constexpr size_t kNoAllocBytes = kNoAllocPos32 + kNoAllocPart + kNoAllocFlags;
@@ -478,7 +481,7 @@ int md_hvp(const md_params* p, const double* pos, const md_cells* cells, const m
     if ((rc = check_slot_list(c, list, false)) != MD_OK) return rc;
     if ((rc = check_ws(c, ws, ws_bytes)) != MD_OK) return rc;
     double* part = dparam ? (double*)((char*)ws + c.W.part_a) : nullptr;
-    MD_HIP(launch_hvp(c.g, c.lj, pos, cells->cell_xyz, *list, u, Hu, part, stream), "md_hvp");
+    MD_HIP(launch_hvp(c.g, c.lj, pos, *cells, *list, u, Hu, part, stream), "md_hvp");
     if (dparam) MD_HIP(launch_reduce_pair(part, c.W.nbf, 1.0, 1.0, dparam, stream), "md_hvp/reduce");
     return MD_OK;
 }
@@ -494,7 +497,7 @@ int md_param_grad(const md_params* p, const double* pos, const md_cells* cells, 
     if ((rc = check_slot_list(c, list, false)) != MD_OK) return rc;
     if ((rc = check_ws(c, ws, ws_bytes)) != MD_OK) return rc;
     double* part = (double*)((char*)ws + c.W.part_a);
-    MD_HIP(launch_param_grad(c.g, c.lj, pos, cells->cell_xyz, *list, part, stream), "md_param_grad");
+    MD_HIP(launch_param_grad(c.g, c.lj, pos, *cells, *list, part, stream), "md_param_grad");
     MD_HIP(launch_reduce_pair(part, c.W.nbf, 1.0, 1.0, dU, stream), "md_param_grad/reduce");
     return MD_OK;
 }
@@ -520,7 +523,7 @@ int md_adjoint_kick(const md_params* p, const double* pos, const md_cells* cells
     k.cU = coef[4];
     k.dt = p->dt;
     double* part = (double*)((char*)ws + c.W.part_a);
-    MD_HIP(launch_adjoint_kick(c.g, c.lj, pos, cells->cell_xyz, *list, u, out, u_out, k, part, stream),
+    MD_HIP(launch_adjoint_kick(c.g, c.lj, pos, *cells, *list, u, out, u_out, k, part, stream),
            "md_adjoint_kick");
     MD_HIP(launch_reduce_pair(part, c.W.nbf, 1.0, 1.0, acc, stream, true), "md_adjoint_kick/reduce");
     return MD_OK;
@@ -641,6 +644,8 @@ static TileIo tile_io(const md_state* st)
         t.start = st->cells.start;
         t.count = st->cells.count;
         t.stage = st->tile_stage;
+    } else {
+        t.order = st->cells.sorted ? nullptr : st->cells.order;
     }
     return t;
 }
@@ -817,7 +822,7 @@ int md_prepare(const md_params* p, md_state* st, hipStream_t s)
     if ((rc = force_eval(c, p, st, true, T, s)) != MD_OK) return rc;
     IntArgs a = int_args(c, p, st, true);
     MD_HIP(launch_integrate(c.g, INT_KE, a, s), "prepare/ke");
-    MD_HIP(launch_reduce_energy((double*)((char*)st->ws + c.W.part_a), force_blocks(c.g, st->list_tiled),
+    MD_HIP(launch_reduce_energy((double*)((char*)st->ws + c.W.part_a), force_blocks(c.g, st->list_tiled != 0, st->list.half != 0),
                                 (double*)((char*)st->ws + c.W.part_b), c.W.nbi, st->energy, nullptr,
                                 (double*)((char*)st->ws + c.W.red), s),
            "prepare/reduce");
@@ -840,7 +845,7 @@ int md_energy(const md_params* p, md_state* st, double* out, hipStream_t s)
     if ((rc = force_eval(c, p, st, true, T, s)) != MD_OK) return rc;
     IntArgs a = int_args(c, p, st, true);
     MD_HIP(launch_integrate(c.g, INT_KE, a, s), "energy/ke");
-    MD_HIP(launch_reduce_energy((double*)((char*)st->ws + c.W.part_a), force_blocks(c.g, st->list_tiled),
+    MD_HIP(launch_reduce_energy((double*)((char*)st->ws + c.W.part_a), force_blocks(c.g, st->list_tiled != 0, st->list.half != 0),
                                 (double*)((char*)st->ws + c.W.part_b), c.W.nbi, st->energy, out,
                                 (double*)((char*)st->ws + c.W.red), s),
            "energy/reduce");
@@ -922,7 +927,7 @@ static int step_runs(const Ctx& c, const md_params* p, md_state* st, int64_t nst
         double* Palt = st->pos_alt;
         float* P32 = st->pos32;
         float* P32alt = st->pos32_alt;
-        const int64_t nfb = force_blocks(c.g, st->list_tiled);
+        const int64_t nfb = force_blocks(c.g, st->list_tiled != 0, st->list.half != 0);
         int64_t k_run = k_log;
         for (int64_t b = 0; b < run; ++b) {
             const int64_t step_no = st->step + 1 + b;
@@ -1119,7 +1124,7 @@ static int step_loop(const md_params* p, md_state* st, int64_t nsteps, int64_t s
         }
         if (sample) {
             tick(T, MD_T_REDUCE, 0, s);
-            const int64_t nfb = force_blocks(c.g, st->list_tiled);
+            const int64_t nfb = force_blocks(c.g, st->list_tiled != 0, st->list.half != 0);
             MD_HIP(launch_reduce_energy(part_pw, nfb, part_ke, nfb, st->energy,
                                         energy_log ? energy_log + 4 * k_log : nullptr,
                                         (double*)((char*)st->ws + c.W.red), s),

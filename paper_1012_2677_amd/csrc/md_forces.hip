@@ -3,10 +3,14 @@
 // registers while its row is walked), optionally fused with the velocity-Verlet
 // kicks and drift that consume the force (Sec. 4.5 integrator).
 //
-// Work layout.  A wave owns 64 consecutive keys: lane L owns key base + L for
+// Work layout.  A wave owns 64 consecutive keys of the cell order (whatever the
+// order of the slots, so that keys walked together share their partners in
+// the caches: mixed with energy, 1.15 million particles in random slot order
+// 752 us in slot order, 320 in cell order): lane L owns key base + L for
 // everything that is per key (row bounds, own coordinates, the force it ends
-// with and the integrator epilogue, all coalesced).  The pair work runs in
-// 8 rounds: in round r the 8 lanes of group q (lanes 8q .. 8q+7) walk the row of
+// with and the integrator epilogue, coalesced when the slots are in cell
+// order).  The pair work runs in
+// 8 rounds (fewer, with as many fewer keys, in small systems): in round r the 8 lanes of group q (lanes 8q .. 8q+7) walk the row of
 // key base + 8r + q together, lane j of the group taking entries j, j+8, ...
 // so each group reads its row as one contiguous run and a round covers 8
 // consecutive keys (consecutive rows; partners in the same few cells).  The wave walks the 8 rows
@@ -70,9 +74,12 @@ struct PairArgs {
     const int32_t* count;
     int32_t tc, nt;            // tiled: cells per tile along z, tiles per column
     const int32_t* gate;       // step passes: nothing to do when *gate != 0
+    const int32_t* order;      // slot lists: slots in cell order (nullptr: they are in it)
+    int32_t rounds;            // slot lists: rounds of 8 keys per wave
 };
 
-// Keys [kb, ke) of logical block b: a chunk of kForceBlock consecutive slots.
+// Keys [kb, ke) of logical block b of a half-list pass: a chunk of kForceBlock
+// consecutive slots.
 __device__ __forceinline__ void block_keys(const PairArgs& a, int64_t b, int64_t& kb, int64_t& ke)
 {
     kb = b * kForceBlock;
@@ -310,19 +317,21 @@ __global__ __launch_bounds__(kForceBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_fp64(
     if (a.gate && a.gate[0]) return;
     const int64_t blk = xcd_remap(blockIdx.x, gridDim.x);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, sub = lane & 7, grp = lane >> 3;
-    int64_t kb, kend;
-    block_keys(a, blk, kb, kend);
+    // the block's places of the cell order: K = 8 rounds per wave
+    const int K = 8 * a.rounds;
+    const int64_t kb = blk * NW * K, kend = kb + NW * K < a.n ? kb + NW * K : a.n;
     const double rc2 = a.lj.rc2, A = a.lj.A, B = a.lj.B, C8 = a.lj.C8;
     double pe = 0.0, w = 0.0, ke = 0.0, d2 = 0.0, v2 = 0.0;
-    // each wave takes 64-key chunks of the block's range (a wave-uniform loop;
-    // the LDS rows below are private to the wave, so no block barrier inside;
-    // written as a loop, which also schedules better than a straight pass)
-    for (int64_t base = kb + wave * 64; base < kend; base += NW * 64) {
-    const int64_t mykey = base + lane;
-    const bool myvalid = mykey < kend;
+    // (a wave-uniform loop of one turn, which schedules better than a straight
+    // pass; the LDS rows below are private to the wave, so no block barrier
+    // inside)
+    for (int64_t base = kb + wave * K; base < kend; base += NW * K) {
+    const bool myvalid = lane < K && base + lane < kend;
+    // lanes past the end load the last key (no branch) and get an empty row
+    const int64_t place = myvalid ? base + lane : kend - 1;
+    const int64_t mykey = a.order ? a.order[place] : place;
     {
-        // lanes past the end load the last key (no branch) and get an empty row
-        const int64_t k = myvalid ? mykey : kend - 1;
+        const int64_t k = mykey;
         double4 p = a.pos[k];
         p.w = (a.exact_all || boundary_cell(a.cell_xyz[k], a.nc)) ? 1.0 : 0.0;
         s_p[wave][lane] = p;
@@ -331,7 +340,7 @@ __global__ __launch_bounds__(kForceBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_fp64(
     }
     __builtin_amdgcn_wave_barrier();
     double kfx = 0.0, kfy = 0.0, kfz = 0.0;
-    for (int r = 0; r < 8; ++r) {
+    for (int r = 0; r < a.rounds; ++r) {
         const int ks = (r << 3) | grp;           // key base + 8 r + grp
         const int cmax = __builtin_amdgcn_readfirstlane(group8_max(s_cnt[wave][(r << 3) | sub]));
         const int cnt = s_cnt[wave][ks];
@@ -433,19 +442,21 @@ __global__ __launch_bounds__(kForceBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_mixed
     __syncthreads();
     const int64_t blk = xcd_remap(blockIdx.x, gridDim.x);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, sub = lane & 7, grp = lane >> 3;
-    int64_t kb, kend;
-    block_keys(a, blk, kb, kend);
+    // the block's places of the cell order: K = 8 rounds per wave
+    const int K = 8 * a.rounds;
+    const int64_t kb = blk * NW * K, kend = kb + NW * K < a.n ? kb + NW * K : a.n;
     const float rc2 = (float)a.lj.rc2, A = (float)a.lj.A, B = (float)a.lj.B, C8 = (float)a.lj.C8;
     double pe = 0.0, w = 0.0, ke = 0.0, d2 = 0.0, v2 = 0.0;
-    // each wave takes 64-key chunks of the block's range (a wave-uniform loop;
-    // the LDS rows below are private to the wave, so no block barrier inside;
-    // written as a loop, which also schedules better than a straight pass)
-    for (int64_t base = kb + wave * 64; base < kend; base += NW * 64) {
-    const int64_t mykey = base + lane;
-    const bool myvalid = mykey < kend;
+    // (a wave-uniform loop of one turn, which schedules better than a straight
+    // pass; the LDS rows below are private to the wave, so no block barrier
+    // inside)
+    for (int64_t base = kb + wave * K; base < kend; base += NW * K) {
+    const bool myvalid = lane < K && base + lane < kend;
+    // lanes past the end load the last key (no branch) and get an empty row
+    const int64_t place = myvalid ? base + lane : kend - 1;
+    const int64_t mykey = a.order ? a.order[place] : place;
     {
-        // lanes past the end load the last key (no branch) and get an empty row
-        const int64_t k = myvalid ? mykey : kend - 1;
+        const int64_t k = mykey;
         float4 l = a.pos32[k];
         l.w = __int_as_float((int)k);   // the key's own slot (stand-in partner)
         s_l[wave][lane] = l;
@@ -454,7 +465,7 @@ __global__ __launch_bounds__(kForceBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_mixed
     }
     __builtin_amdgcn_wave_barrier();
     float kfx = 0.f, kfy = 0.f, kfz = 0.f;
-    for (int r = 0; r < 8; ++r) {
+    for (int r = 0; r < a.rounds; ++r) {
         const int ks = (r << 3) | grp;           // key base + 8 r + grp
         const int cmax = __builtin_amdgcn_readfirstlane(group8_max(s_cnt[wave][(r << 3) | sub]));
         const int cnt = s_cnt[wave][ks];
@@ -1129,9 +1140,25 @@ __global__ __launch_bounds__(kTileBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_tiled(
     if (ENERGY || MODE == MODE_KKD) block_epilogue<ENERGY, MODE, VMAX, NW>(a, blk, pe, w, ke, d2, v2);
 }
 
-int64_t pair_blocks(const Geo& g) { return ceil_div(g.n, kForceBlock); }
+// Rounds per wave of the slot-list passes: the most that still give the chip
+// kPairBlocks blocks of four waves.  A wave's rounds follow one another, each
+// with two dependent trips to memory (row entries, partners), so that small
+// systems are bound by that chain: FP64 with energy, 2048 particles, 8 rounds
+// 22.8 us, 1 round 9.  (512 and 2048 blocks instead of 1024: the same within
+// noise at 4,000, 62,000 and 256,000 particles.)
+constexpr int64_t kPairBlocks = 1024;
+static int pair_rounds(const Geo& g)
+{
+    int r = 8;
+    while (r > 1 && g.n < kPairBlocks * (kForceBlock / 8) * r) r >>= 1;
+    return r;
+}
+int64_t pair_blocks(const Geo& g) { return ceil_div(g.n, (kForceBlock / 8) * pair_rounds(g)); }
 
-int64_t force_blocks(const Geo& g, bool tiled) { return tiled ? g.ntile : pair_blocks(g); }
+int64_t force_blocks(const Geo& g, bool tiled, bool half)
+{
+    return tiled ? g.ntile : (half ? ceil_div(g.n, kForceBlock) : pair_blocks(g));
+}
 
 static PairArgs make_pair_args(const Geo& g, const LJ& lj, const double* pos, const float* pos32,
                                const int32_t* cell_xyz, const md_pairlist& list)
@@ -1152,6 +1179,7 @@ static PairArgs make_pair_args(const Geo& g, const LJ& lj, const double* pos, co
         a.nc[k] = g.nc[k];
     }
     a.exact_all = g.force_minimg_all;
+    a.rounds = pair_rounds(g);
     a.tc = g.tc;
     a.nt = g.nt;
     a.lj = lj;
@@ -1190,7 +1218,7 @@ static hipError_t launch_pairs_half(const Geo& g, int precision, const PairArgs&
 {
     const int64_t words = (precision == MD_MIXED ? 3 : 6) * g.n;
     if (hipError_t e = launch_fill_i32((int32_t*)a.force, 0, words, s)) return e;
-    const dim3 grid((unsigned)pair_blocks(g)), block(kForceBlock);
+    const dim3 grid((unsigned)force_blocks(g, false, true)), block(kForceBlock);
     if (precision == MD_MIXED)
         hipLaunchKernelGGL((k_pairs_half<kForceUnroll, ENERGY, true>), grid, block, 0, s, a);
     else
@@ -1201,7 +1229,7 @@ static hipError_t launch_pairs_half(const Geo& g, int precision, const PairArgs&
 template <int MODE, bool VMAX, bool ENERGY>
 static void launch_integrate_half(const Geo& g, int precision, const PairArgs& a, hipStream_t s)
 {
-    const dim3 grid((unsigned)pair_blocks(g)), block(kForceBlock);
+    const dim3 grid((unsigned)force_blocks(g, false, true)), block(kForceBlock);
     if (precision == MD_MIXED)
         hipLaunchKernelGGL((k_integrate_half<MODE, true, VMAX, ENERGY>), grid, block, 0, s, a);
     else
@@ -1223,6 +1251,7 @@ hipError_t launch_forces(const Geo& g, const LJ& lj, int precision, const double
     PairArgs a = make_pair_args(g, lj, pos, pos32, cell_xyz, list);
     a.start = tio.start;
     a.count = tio.count;
+    a.order = tio.order;
     a.force = out.force;
     a.part_pw = out.part;
     a.flags = out.flags;
@@ -1243,6 +1272,7 @@ hipError_t launch_force_step(const Geo& g, const LJ& lj, int precision, const St
     PairArgs a = make_pair_args(g, lj, io.pos, io.pos32, io.cell_xyz, io.list);
     a.start = io.tile.start;
     a.count = io.tile.count;
+    a.order = io.tile.order;
     a.force = io.force;
     a.part_pw = io.part_pw;
     a.part_ke = io.part_ke;

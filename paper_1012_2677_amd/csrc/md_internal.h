@@ -322,12 +322,14 @@ struct ForceOut {
     double* part;       // per-block (PE, W) partials, or nullptr
     int64_t* flags;     // [0] |= 1 on a non-finite force
 };
-// Tiled lists (mixed only) need cells (start / count) and the largest staged
-// count (tile_stage); tile_stage = 0 selects the list of slot entries.
+// Tiled lists need cells (start / count) and the largest staged count
+// (tile_stage); tile_stage = 0 selects the list of slot entries, whose keys are
+// walked in cell order (order: the slots in it, nullptr when they are in it).
 struct TileIo {
     const int32_t* start = nullptr;
     const int32_t* count = nullptr;
     int32_t stage = 0;
+    const int32_t* order = nullptr;
 };
 hipError_t launch_forces(const Geo& g, const LJ& lj, int precision, const double* pos,
                          const float* pos32, const int32_t* cell_xyz, const md_pairlist& list,
@@ -359,7 +361,7 @@ struct StepIo {
 };
 hipError_t launch_force_step(const Geo& g, const LJ& lj, int precision, const StepIo& io, hipStream_t s);
 int64_t pair_blocks(const Geo& g);   // blocks (and energy partials) of one pair-kernel launch
-int64_t force_blocks(const Geo& g, bool tiled);   // same for either list layout
+int64_t force_blocks(const Geo& g, bool tiled, bool half);   // same for every list layout
 
 // md_integrate.hip
 enum IntMode { INT_KD = 0, INT_KE = 1 };
@@ -417,17 +419,17 @@ hipError_t launch_ldc_check(const Geo& g, const double* pos, const double* pos_r
                             unsigned long long* flag, hipStream_t s);
 
 // md_adjoint.hip
-hipError_t launch_hvp(const Geo& g, const LJ& lj, const double* pos, const int32_t* cell_xyz,
+hipError_t launch_hvp(const Geo& g, const LJ& lj, const double* pos, const md_cells& cells,
                       const md_pairlist& list, const double* u, double* Hu, double* part,
                       hipStream_t s);
 struct AdjCoef {
     double alpha, beta, gamma, cu, cU, dt;
 };
-hipError_t launch_adjoint_kick(const Geo& g, const LJ& lj, const double* pos, const int32_t* cell_xyz,
+hipError_t launch_adjoint_kick(const Geo& g, const LJ& lj, const double* pos, const md_cells& cells,
                                const md_pairlist& list, const double* u, double* out, double* u_out,
                                const AdjCoef& k, double* part, hipStream_t s);
 hipError_t launch_param_grad(const Geo& g, const LJ& lj, const double* pos,
-                             const int32_t* cell_xyz, const md_pairlist& list, double* part,
+                             const md_cells& cells, const md_pairlist& list, double* part,
                              hipStream_t s);
 
 }  // namespace md
