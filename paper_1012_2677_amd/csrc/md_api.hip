@@ -138,8 +138,14 @@ static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 //   [16..31]  flags gathered for one read-back (layout in k_gather_flags)
 constexpr int kScalOut = 16;
 
-WsLayout ws_layout(const Geo& g, int64_t ldc_max, int precision)
+// Fewer particles than this fit the vector caches whole, and the launch that
+// packs their records costs more than they save (2048: 6.5 us without, 6.2 and
+// 2.8 with; 62,000: 93 us without, 35 and 3.4 with, cell order included).
+constexpr int64_t kRecMinN = 16384;
+
+WsLayout ws_layout(const Geo& g, const md_params& p)
 {
+    const int64_t ldc_max = p.ldc_max;
     const int64_t n = g.n, ncell = g.ncell;
     WsLayout L;
     L.nbs = ceil_div(ncell, kScanItems);
@@ -155,7 +161,9 @@ WsLayout ws_layout(const Geo& g, int64_t ldc_max, int precision)
     L.part_a = off;    off = align256(off + sizeof(double) * 2 * (size_t)std::max(L.nbf, np));
     L.part_b = off;    off = align256(off + sizeof(double) * (size_t)(np > L.nbi ? np : L.nbi));
     // local coordinates of md_forces in mixed precision only
-    L.pos32 = off;     off = align256(off + (precision == MD_MIXED ? 16 * (size_t)n : 0));
+    L.pos32 = off;     off = align256(off + (p.precision == MD_MIXED ? 16 * (size_t)n : 0));
+    L.has_rec = p.precision == MD_FP64 && p.resort_every == 0 && n >= kRecMinN;
+    L.rec = off;       off = align256(off + (L.has_rec ? 48 * (size_t)n : 0));
     L.red = off;       off = align256(off + sizeof(int64_t) * 2 * 1024);
     L.ldc = off;       off = align256(off + sizeof(int32_t) * (size_t)(ldc_max > 0 ? ldc_max : 1));
     L.scal = off;      off = align256(off + sizeof(int64_t) * 32);
@@ -179,7 +187,7 @@ static int setup(const md_params* p, Ctx& c)
     if (rc != MD_OK) return rc;
     c.g = make_geo(*p, c.nc);
     c.lj = make_lj(*p);
-    c.W = ws_layout(c.g, p->ldc_max, p->precision);
+    c.W = ws_layout(c.g, *p);
     return MD_OK;
 }
 
@@ -324,7 +332,7 @@ size_t md_workspace_bytes(const md_params* p)
 {
     int32_t nc[3];
     if (check_params(p, nc) != MD_OK) return 0;
-    return ws_layout(make_geo(*p, nc), p->ldc_max, p->precision).total;
+    return ws_layout(make_geo(*p, nc), *p).total;
 }
 
 int md_pack_positions(const md_params* p, const double* q, double* pos, hipStream_t stream)
@@ -470,6 +478,11 @@ int md_forces_noalloc(const md_params* p, const double* pos, const md_cells* cel
                        (int64_t*)(w + kNoAllocPos32 + kNoAllocPart), stream);
 }
 
+static double* adj_records(const Ctx& c, void* ws)
+{
+    return c.W.has_rec ? (double*)((char*)ws + c.W.rec) : nullptr;
+}
+
 int md_hvp(const md_params* p, const double* pos, const md_cells* cells, const md_pairlist* list,
            const double* u, double* Hu, double* dparam, void* ws, size_t ws_bytes, hipStream_t stream)
 {
@@ -481,7 +494,7 @@ int md_hvp(const md_params* p, const double* pos, const md_cells* cells, const m
     if ((rc = check_slot_list(c, list, false)) != MD_OK) return rc;
     if ((rc = check_ws(c, ws, ws_bytes)) != MD_OK) return rc;
     double* part = dparam ? (double*)((char*)ws + c.W.part_a) : nullptr;
-    MD_HIP(launch_hvp(c.g, c.lj, pos, *cells, *list, u, Hu, part, stream), "md_hvp");
+    MD_HIP(launch_hvp(c.g, c.lj, pos, *cells, *list, u, Hu, part, adj_records(c, ws), stream), "md_hvp");
     if (dparam) MD_HIP(launch_reduce_pair(part, c.W.nbf, 1.0, 1.0, dparam, stream), "md_hvp/reduce");
     return MD_OK;
 }
@@ -523,7 +536,7 @@ int md_adjoint_kick(const md_params* p, const double* pos, const md_cells* cells
     k.cU = coef[4];
     k.dt = p->dt;
     double* part = (double*)((char*)ws + c.W.part_a);
-    MD_HIP(launch_adjoint_kick(c.g, c.lj, pos, *cells, *list, u, out, u_out, k, part, stream),
+    MD_HIP(launch_adjoint_kick(c.g, c.lj, pos, *cells, *list, u, out, u_out, k, part, adj_records(c, ws), stream),
            "md_adjoint_kick");
     MD_HIP(launch_reduce_pair(part, c.W.nbf, 1.0, 1.0, acc, stream, true), "md_adjoint_kick/reduce");
     return MD_OK;

@@ -144,6 +144,7 @@ struct WsLayout {
     size_t part_a;     // double[2*nbf]  per-block partial sums (force kernels)
     size_t part_b;     // double[nbi]    per-block partial sums (streaming kernels)
     size_t pos32;      // float4[n]      mixed-mode local coordinates (md_forces; empty in FP64)
+    size_t rec;        // double[6 n]    records of the adjoint passes (FP64 without re-sorts; else empty)
     size_t red;        // int64[2*1024]  partials of the list statistics
     size_t ldc;        // int32[ldc_max] members of the large-displacement check
     size_t scal;       // int64[32]      small device scalars (layout in md_api.hip)
@@ -151,11 +152,12 @@ struct WsLayout {
     size_t mx;         // int64[2][kMaxSlots * kMaxSlotStride]  block maxima of d2 and v2
     size_t tile_used;  // int32[ntile]   entries taken in each tile's pooled block (tiled list build)
     size_t total;
+    bool has_rec;      // the adjoint passes run on slot lists, which a re-sorting state does not keep
     int64_t nbs;       // scan blocks
     int64_t nbf;       // adjoint-kernel blocks (kKeysPerBlock keys each)
     int64_t nbi;       // streaming-kernel blocks
 };
-WsLayout ws_layout(const Geo& g, int64_t ldc_max, int precision);
+WsLayout ws_layout(const Geo& g, const md_params& p);
 
 // ---------------------------------------------------------------------------
 // Small device helpers
@@ -421,13 +423,13 @@ hipError_t launch_ldc_check(const Geo& g, const double* pos, const double* pos_r
 // md_adjoint.hip
 hipError_t launch_hvp(const Geo& g, const LJ& lj, const double* pos, const md_cells& cells,
                       const md_pairlist& list, const double* u, double* Hu, double* part,
-                      hipStream_t s);
+                      double* rec, hipStream_t s);
 struct AdjCoef {
     double alpha, beta, gamma, cu, cU, dt;
 };
 hipError_t launch_adjoint_kick(const Geo& g, const LJ& lj, const double* pos, const md_cells& cells,
                                const md_pairlist& list, const double* u, double* out, double* u_out,
-                               const AdjCoef& k, double* part, hipStream_t s);
+                               const AdjCoef& k, double* part, double* rec, hipStream_t s);
 hipError_t launch_param_grad(const Geo& g, const LJ& lj, const double* pos,
                              const md_cells& cells, const md_pairlist& list, double* part,
                              hipStream_t s);
