@@ -67,6 +67,8 @@ static int check_params(const md_params* p, int32_t nc[3])
     return MD_OK;
 }
 
+constexpr int64_t kTilesFew = 256;
+
 Geo make_geo(const md_params& p, const int32_t nc[3])
 {
     Geo g;
@@ -82,14 +84,26 @@ Geo make_geo(const md_params& p, const int32_t nc[3])
         if (nc[k] < 5) g.exact_all = 1;
     }
     g.force_minimg_all = g.exact_all || p.rebuild_rule == MD_REBUILD_DUTC_LDC;
-    // tiles: about kTileKeys keys each at the mean density, at most nz - 2
-    // cells long so that a tile's runs wrap at most once
+    // tiles: at most about kTileKeys keys each at the mean density, and at most
+    // nz - 2 cells long so that a tile's runs wrap at most once.  A column is
+    // cut into tiles of equal length rather than full ones and a rest, whose
+    // short tiles would stage two extra cells per column for few keys (force
+    // pass, FP64: 28 cells as 10 + 10 + 8 40.4 us, as 13 + 13 + 2 45.1; 14 as
+    // 7 + 7 15.8, as 12 + 2 18.1; 71 as 5 x 12 + 11 429, as 5 x 13 + 6 436;
+    // mixed: 28 as 14 + 14 29.9, as 17 + 11 32.2), and grids of fewer tiles
+    // than the chip has CUs into shorter ones, down to the 64 keys that the
+    // four waves of a tile take in one round (8 x 8 x 8 cells of 21 particles,
+    // mixed: tiles of 4, 3, 2, 1 cells 14.8, 14.7, 13.1, 13.6 us).
     const int nz = nc[2];
     int tc = p.tile_cells;
     if (tc == 0) {
-        const double mean = (double)p.n / (double)g.ncell;
+        const double mean = std::max((double)p.n / (double)g.ncell, 1e-9);
         const int keys = p.precision == MD_MIXED ? kTileKeys : kTileKeys64;
-        tc = (int)std::lround((double)keys / (mean > 1e-9 ? mean : 1e-9));
+        const double most = std::min(std::max(std::round((double)keys / mean), 1.0), 1024.0);
+        int64_t nt = ceil_div(nz, (int64_t)most);
+        auto cells = [&] { return (int)std::min<int64_t>(ceil_div(nz, nt), nz - 2); };
+        while (cells() * mean > 64.0 && cells() > 1 && (int64_t)nc[0] * nc[1] * ceil_div(nz, cells()) < kTilesFew) ++nt;
+        tc = cells();
     }
     tc = std::max(1, std::min(tc, nz - 2));
     const bool tiles = p.list_layout == MD_LIST_AUTO;
