@@ -389,9 +389,9 @@ int md_prepare(const md_params* p, md_state* st, hipStream_t stream);
  * energy_log[k][0..3] = (KE, PE, W, KE + PE) is written (device double
  * array; NULL to skip; sample_every <= 0 samples nothing).
  * With MD_REBUILD_HALF_SKIN and a full list the rebuild decision is taken on
- * the device: steps are queued in runs (md_params.step_run), a small pass
- * after each step sets a device flag once the next step must rebuild, the
- * passes of the run's later steps then do nothing, and the host waits once
+ * the device: steps are queued in runs (md_params.step_run), the passes of a
+ * step first read the largest displacement that the step before left and do
+ * nothing once a step must rebuild, and the host waits once
  * per run and once per rebuild, resuming where the run stopped.  With
  * MD_REBUILD_DUTC_LDC or a half list it waits once per step.
  * On MD_ERR_CAPACITY the state stops in phase 1 with st->step steps done;

@@ -148,7 +148,7 @@ static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 //   [0], [1]  cell-grid error flags         [2]  md_forces non-finite flag
 //   [4]       large-displacement members    [5]  large-displacement violation
 //   [6]       largest squared displacement (md_ldc_check)
-//   [8]       gate of a run of queued steps (int32; md_step)
+//   [8]       gate of a run of queued steps (int32[2]; md_step)
 //   [16..31]  flags gathered for one read-back (layout in k_gather_flags)
 constexpr int kScalOut = 16;
 
@@ -880,10 +880,10 @@ int md_energy(const md_params* p, md_state* st, double* out, hipStream_t s)
 }
 
 // Steps of the half-skin rule with a full list, queued in runs without a host
-// wait per step.  The gather after each step decides on the device whether
-// the next one must rebuild first (Sec. 2.3: largest displacement since the
-// build beyond half the skin); once one must, it sets the gate and the passes
-// of the rest of the run do nothing.  The host waits once per run, learns how
+// wait per step.  The passes of a step decide on the device whether it must
+// rebuild first (Sec. 2.3: largest displacement since the build beyond half the
+// skin); once one must, the passes of the rest of the run do nothing.  The host
+// waits once per run, learns how
 // many steps ran, rebuilds when the run stopped for it, and resumes there: the
 // steps taken, the lists and the results are those of one wait per step.
 static_assert(MD_STEP_RUN_MAX <= kTimerSlots, "a run's launches must fit the timer slots");
@@ -909,6 +909,7 @@ static int step_runs(const Ctx& c, const md_params* p, md_state* st, int64_t nst
         tick(T, MD_T_INTEGRATE, 1, s);
         st->phase = 1;
     }
+    MD_HIP(launch_fill_i32(gate, 0, 2, s), "step/gate");
     if ((rc = read_flags(c, st, s, f)) != MD_OK) return rc;
     timer_collect(T);
     double maxd2;
@@ -955,14 +956,24 @@ static int step_runs(const Ctx& c, const md_params* p, md_state* st, int64_t nst
         float* P32 = st->pos32;
         float* P32alt = st->pos32_alt;
         const int64_t nfb = force_blocks(c.g, st->list_tiled != 0, st->list.half != 0);
+        const bool folded = nfb <= kFoldBlocks;
+        FlagGate fg;
+        fg.run.slots = folded ? mx_slots(c, st, 0) : nullptr;
+        fg.run.gate = gate;
+        fg.run.thr2 = thr2;
         int64_t k_run = k_log;
         for (int64_t b = 0; b < run; ++b) {
             const int64_t step_no = st->step + 1 + b;
             const bool sample = sample_every > 0 && (step_no % sample_every) == 0;
             const bool last = done + b + 1 == nsteps;
             const int32_t* g = b > 0 ? gate : nullptr;
+            RunIo rio;
+            rio.slots = folded ? mx_slots(c, st, 0) : nullptr;
+            rio.gate = gate;
+            rio.idx = (int32_t)b;
+            rio.thr2 = thr2;
             if (traj)
-                MD_HIP(launch_record(c.g, P, st->id, traj + 4 * c.g.n * (done + b), s, g), "step/record");
+                MD_HIP(launch_record(c.g, P, st->id, traj + 4 * c.g.n * (done + b), s, rio), "step/record");
             StepIo io;
             io.pos = P;
             io.pos32 = mixed ? P32 : nullptr;
@@ -982,7 +993,7 @@ static int step_runs(const Ctx& c, const md_params* p, md_state* st, int64_t nst
             io.drift = !last;
             io.track_speed = false;
             io.tile = tile_io(st);
-            io.gate = g;
+            io.run = rio;
             tick(T, MD_T_FORCE, 0, s);
             MD_HIP(launch_force_step(c.g, c.lj, p->precision, io, s), "step/force");
             tick(T, MD_T_FORCE, 1, s);
@@ -999,16 +1010,14 @@ static int step_runs(const Ctx& c, const md_params* p, md_state* st, int64_t nst
                 tick(T, MD_T_REDUCE, 1, s);
                 ++k_run;
             }
-            FlagGate fg;
-            fg.gate = gate;
-            fg.thr2 = thr2;
-            fg.idx = (int32_t)(b + 1);
-            fg.fold = !last;     // the last step of a call has no drift
-            fg.clear = !last;
-            MD_HIP(launch_gather_flags(st->list.status, scal, st->flags, st->energy,
-                                       (const int64_t*)((char*)st->ws + c.W.tmax), mx_slots(c, st, 0),
-                                       scal + kScalOut, s, fg),
-                   "step/gather");
+            if (!folded || b + 1 == run) {
+                fg.run.idx = (int32_t)(b + 1);
+                fg.drift = !last;     // the last step of a call has no drift
+                MD_HIP(launch_gather_flags(st->list.status, scal, st->flags, st->energy,
+                                           (const int64_t*)((char*)st->ws + c.W.tmax), mx_slots(c, st, 0),
+                                           scal + kScalOut, s, fg),
+                       "step/gather");
+            }
         }
         int64_t* dst = st->host_scratch ? st->host_scratch : f;
         MD_HIP(hipMemcpyAsync(dst, scal + kScalOut, 16 * sizeof(int64_t), hipMemcpyDeviceToHost, s), "step/copy");

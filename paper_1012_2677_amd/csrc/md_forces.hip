@@ -73,7 +73,8 @@ struct PairArgs {
     const int32_t* start;      // tiled: cell starts and counts (slots in cell order)
     const int32_t* count;
     int32_t tc, nt;            // tiled: cells per tile along z, tiles per column
-    const int32_t* gate;       // step passes: nothing to do when *gate != 0
+    RunIo run;                 // step passes: their run of queued steps
+    int32_t max_slots;         // slots that the block maxima are spread over
     const int32_t* order;      // slot lists: slots in cell order (nullptr: they are in it)
     int32_t rounds;            // slot lists: rounds of 8 keys per wave
 };
@@ -223,10 +224,19 @@ __device__ __forceinline__ void block_epilogue(const PairArgs& a, int64_t blk, d
             if (MODE != MODE_FORCE) a.part_ke[blk] = 0.5 * ske;
         }
         if (MODE == MODE_KKD) {
-            atomicMax(max_slot(a.max_d2, blk), (unsigned long long)__double_as_longlong(m));
-            if (VMAX) atomicMax(max_slot(a.max_v2, blk), (unsigned long long)__double_as_longlong(mv));
+            atomicMax(max_slot(a.max_d2, blk, a.max_slots), (unsigned long long)__double_as_longlong(m));
+            if (VMAX) atomicMax(max_slot(a.max_v2, blk, a.max_slots), (unsigned long long)__double_as_longlong(mv));
         }
     }
+}
+
+// A non-finite force: the state's flag and, in a run of queued steps, the mark
+// that stops the steps after this one.
+template <bool FOLD = true>
+__device__ __forceinline__ void mark_nonfinite(const PairArgs& a, int64_t blk)
+{
+    atomicOr((unsigned long long*)a.flags, 1ull);
+    if (FOLD && a.run.slots) atomicOr(max_slot(run_set(a.run, a.run.idx), blk, kRunSlots) + 1, 1ull);
 }
 
 // Integrator epilogue of one key (lane): kicks, drift, wrap, displacement since
@@ -314,7 +324,9 @@ __global__ __launch_bounds__(kForceBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_fp64(
     __shared__ double4 s_p[NW][64];     // own position, .w = 1 if the key needs minimum images
     __shared__ int64_t s_off[NW][64];
     __shared__ int32_t s_cnt[NW][64];
-    if (a.gate && a.gate[0]) return;
+    if (!a.run.slots && a.run.idx > 0 && a.run.gate[0]) return;
+    RunCheck chk;
+    if (a.run.slots) chk = run_check_load(a.run);
     const int64_t blk = xcd_remap(blockIdx.x, gridDim.x);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, sub = lane & 7, grp = lane >> 3;
     // the block's places of the cell order: K = 8 rounds per wave
@@ -322,6 +334,11 @@ __global__ __launch_bounds__(kForceBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_fp64(
     const int64_t kb = blk * NW * K, kend = kb + NW * K < a.n ? kb + NW * K : a.n;
     const double rc2 = a.lj.rc2, A = a.lj.A, B = a.lj.B, C8 = a.lj.C8;
     double pe = 0.0, w = 0.0, ke = 0.0, d2 = 0.0, v2 = 0.0;
+    if (a.run.slots) {
+        const bool stop = run_stopped(a.run, chk);
+        if (blockIdx.x == 0 && wave == 0) run_mark(a.run, chk, stop);
+        if (stop) return;
+    }
     // (a wave-uniform loop of one turn, which schedules better than a straight
     // pass; the LDS rows below are private to the wave, so no block barrier
     // inside)
@@ -403,7 +420,7 @@ __global__ __launch_bounds__(kForceBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_fp64(
         }
     }
     if (myvalid) {
-        if (!isfinite(kfx + kfy + kfz)) atomicOr((unsigned long long*)a.flags, 1ull);
+        if (!isfinite(kfx + kfy + kfz)) mark_nonfinite(a, blk);
         if (MODE != MODE_KKD) {
             double* F = (double*)a.force;
             F[mykey] = kfx;
@@ -431,7 +448,9 @@ __global__ __launch_bounds__(kForceBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_mixed
     __shared__ float4 s_l[NW][64];
     __shared__ int64_t s_off[NW][64];
     __shared__ int32_t s_cnt[NW][64];
-    if (a.gate && a.gate[0]) return;
+    if (!a.run.slots && a.run.idx > 0 && a.run.gate[0]) return;
+    RunCheck chk;
+    if (a.run.slots) chk = run_check_load(a.run);
     if (threadIdx.x < 32) {
         // code 27 never occurs in an entry: it is the stand-in used for
         // masked slots, displaced far beyond the cutoff
@@ -447,6 +466,11 @@ __global__ __launch_bounds__(kForceBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_mixed
     const int64_t kb = blk * NW * K, kend = kb + NW * K < a.n ? kb + NW * K : a.n;
     const float rc2 = (float)a.lj.rc2, A = (float)a.lj.A, B = (float)a.lj.B, C8 = (float)a.lj.C8;
     double pe = 0.0, w = 0.0, ke = 0.0, d2 = 0.0, v2 = 0.0;
+    if (a.run.slots) {
+        const bool stop = run_stopped(a.run, chk);
+        if (blockIdx.x == 0 && wave == 0) run_mark(a.run, chk, stop);
+        if (stop) return;
+    }
     // (a wave-uniform loop of one turn, which schedules better than a straight
     // pass; the LDS rows below are private to the wave, so no block barrier
     // inside)
@@ -519,7 +543,7 @@ __global__ __launch_bounds__(kForceBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_mixed
         }
     }
     if (myvalid) {
-        if (!isfinite(kfx + kfy + kfz)) atomicOr((unsigned long long*)a.flags, 1ull);
+        if (!isfinite(kfx + kfy + kfz)) mark_nonfinite(a, blk);
         if (MODE != MODE_KKD) {
             float* F = (float*)a.force;
             F[mykey] = kfx;
@@ -814,7 +838,7 @@ struct TileT<false> {
     __device__ static uint32_t off(uint32_t e) { return e + (e >> 1); }
 };
 
-template <int U, bool ENERGY, int MODE, bool VMAX, bool MIXED>
+template <int U, bool ENERGY, int MODE, bool VMAX, bool MIXED, bool FOLD>
 __global__ __launch_bounds__(kTileBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_tiled(PairArgs a)
 {
     using R = typename TileT<MIXED>::R;
@@ -826,7 +850,7 @@ __global__ __launch_bounds__(kTileBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_tiled(
     __shared__ uint8_t s_perm[NW][64];
     __shared__ int32_t s_run[9][4];
     __shared__ int32_t s_base[10];
-    if (a.gate && a.gate[0]) return;
+    if (!FOLD && a.run.idx > 0 && a.run.gate[0]) return;
     const int64_t blk = xcd_remap(blockIdx.x, gridDim.x);
     const int nx = a.nc[0], ny = a.nc[1], nz = a.nc[2];
     const int tz = (int)(blk % a.nt);
@@ -851,7 +875,21 @@ __global__ __launch_bounds__(kTileBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_tiled(
         s_run[tid][2] = r.sB;
         s_run[tid][3] = r.lenB;
     }
-    __syncthreads();
+    if constexpr (FOLD) {
+        // the second wave decides for the block whether the run has stopped,
+        // while the first loads the tile's runs
+        __shared__ int s_stop;
+        if (tid >= 64 && tid < 128) {
+            const RunCheck chk = run_check_load(a.run);
+            const bool stop = run_stopped(a.run, chk);
+            if (blockIdx.x == 0) run_mark(a.run, chk, stop);
+            if (tid == 64) s_stop = stop;
+        }
+        __syncthreads();
+        if (s_stop) return;
+    } else {
+        __syncthreads();
+    }
     if (tid == 0) {
         int b = 0;
         for (int col = 0; col < 9; ++col) {
@@ -1120,7 +1158,7 @@ __global__ __launch_bounds__(kTileBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_tiled(
         }
     }
     if (myvalid) {
-        if (!isfinite(kfx + kfy + kfz)) atomicOr((unsigned long long*)a.flags, 1ull);
+        if (!isfinite(kfx + kfy + kfz)) mark_nonfinite<FOLD>(a, blk);
         if (MODE != MODE_KKD) {
             R* F = (R*)a.force;
             F[mykey] = kfx;
@@ -1180,6 +1218,7 @@ static PairArgs make_pair_args(const Geo& g, const LJ& lj, const double* pos, co
     }
     a.exact_all = g.force_minimg_all;
     a.rounds = pair_rounds(g);
+    a.max_slots = kMaxSlots;
     a.tc = g.tc;
     a.nt = g.nt;
     a.lj = lj;
@@ -1197,13 +1236,20 @@ template <bool ENERGY, int MODE, bool VMAX = false>
 static void launch_pairs_mode(const Geo& g, int precision, const PairArgs& a, hipStream_t s, int stage)
 {
     if (stage > 0) {
-        if (precision == MD_MIXED)
-            hipLaunchKernelGGL((k_pairs_tiled<kForceUnroll, ENERGY, MODE, VMAX, true>), dim3((unsigned)g.ntile),
-                               dim3(kTileBlock), sizeof(float4) * (size_t)(stage + 1), s, a);
-        else
-            hipLaunchKernelGGL((k_pairs_tiled<kForceUnroll64, ENERGY, MODE, VMAX, false>), dim3((unsigned)g.ntile),
-                               dim3(kTileBlock), sizeof(D3) * (size_t)(stage + 1), s, a);
-        return;
+        const dim3 grid((unsigned)g.ntile), block(kTileBlock);
+        auto launch = [&](auto fold) {
+            constexpr bool F = decltype(fold)::value;
+            if (precision == MD_MIXED)
+                hipLaunchKernelGGL((k_pairs_tiled<kForceUnroll, ENERGY, MODE, VMAX, true, F>), grid, block,
+                                   sizeof(float4) * (size_t)(stage + 1), s, a);
+            else
+                hipLaunchKernelGGL((k_pairs_tiled<kForceUnroll64, ENERGY, MODE, VMAX, false, F>), grid, block,
+                                   sizeof(D3) * (size_t)(stage + 1), s, a);
+        };
+        if constexpr (MODE != MODE_FORCE && !VMAX) {
+            if (a.run.slots) return launch(std::true_type());
+        }
+        return launch(std::false_type());
     }
     const dim3 grid((unsigned)pair_blocks(g)), block(kForceBlock);
     if (precision == MD_MIXED)
@@ -1286,7 +1332,7 @@ hipError_t launch_force_step(const Geo& g, const LJ& lj, int precision, const St
     a.dt = io.dt;
     const bool energy = io.part_pw != nullptr;
     if (io.list.half) {
-        if (io.gate) return hipErrorInvalidValue;   // the half-list passes take no gate
+        if (io.run.gate) return hipErrorInvalidValue;   // the half-list passes take no part in runs
         // pair pass into the cleared force array, then the integrator
         if (io.tile.stage > 0 || !io.force) return hipErrorInvalidValue;
         hipError_t e = energy ? launch_pairs_half<true>(g, precision, a, s)
@@ -1304,7 +1350,11 @@ hipError_t launch_force_step(const Geo& g, const LJ& lj, int precision, const St
         }
         return hipGetLastError();
     }
-    a.gate = io.gate;
+    a.run = io.run;
+    if (io.run.slots) {
+        a.max_d2 = run_set(io.run, io.run.idx);
+        a.max_slots = kRunSlots;
+    }
     if (io.drift && io.track_speed) {
         // the largest drift speed is needed by the DUTC rule only
         if (energy) launch_pairs_mode<true, MODE_KKD, true>(g, precision, a, s, io.tile.stage);

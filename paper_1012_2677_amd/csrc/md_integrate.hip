@@ -347,19 +347,30 @@ __global__ void k_gather_flags(const int64_t* __restrict__ status, const int64_t
                                const int64_t* __restrict__ tmax, unsigned long long* __restrict__ mx,
                                int64_t* __restrict__ out, FlagGate g)
 {
-    // a run already stopped: leave out (and the slots) as the stopping gather left them
-    if (g.gate && g.gate[0] && g.idx > 1) return;
     // wave-wide maxima over the slots: largest staged tile neighbourhood,
     // largest squared displacement and drift speed (bit patterns of
     // non-negative doubles order like the values)
+    const bool step = g.run.gate != nullptr, folded = g.run.slots != nullptr;
+    const int32_t stopped = step && (folded || g.run.idx > 1) ? g.run.gate[0] : 0;
+    // a run already stopped: leave out (and the slots) as the stopping gather left them
+    if (stopped && !folded) return;
+    const int32_t ran = stopped ? g.run.gate[1] : g.run.idx;
+    const bool fold = !step || stopped || g.drift;
     int64_t m = 0;
     unsigned long long md = 0, mv = 0;
     for (int k = threadIdx.x; k < kTileMaxSlots; k += 64) m = max(m, tmax[k]);
-    if (g.fold) {
+    if (folded) {
+        // the displacements of the last step that ran, set (ran - 1) % 3
+        if (threadIdx.x < kRunSlots) {
+            if (fold) md = run_set(g.run, ran + 2)[threadIdx.x * kMaxSlotStride];
+            for (int k = 0; k < 3; ++k)
+                *(ulonglong2*)(run_set(g.run, k) + threadIdx.x * kMaxSlotStride) = make_ulonglong2(0ull, 0ull);
+        }
+    } else if (fold) {
         for (int k = threadIdx.x; k < kMaxSlots; k += 64) {
             md = max(md, mx[k * kMaxSlotStride]);
             mv = max(mv, mx[(kMaxSlots + k) * kMaxSlotStride]);
-            if (g.clear) {
+            if (step) {
                 mx[k * kMaxSlotStride] = 0;
                 mx[(kMaxSlots + k) * kMaxSlotStride] = 0;
             }
@@ -372,7 +383,7 @@ __global__ void k_gather_flags(const int64_t* __restrict__ status, const int64_t
         mv = max(mv, (unsigned long long)__shfl_xor((long long)mv, o, 64));
     }
     if (threadIdx.x != 0) return;
-    if (g.fold) {
+    if (fold) {
         energy[4] = __longlong_as_double((long long)md);
         energy[5] = __longlong_as_double((long long)mv);
     }
@@ -388,13 +399,10 @@ __global__ void k_gather_flags(const int64_t* __restrict__ status, const int64_t
     out[9] = err[4];    // large-displacement check: member count
     out[10] = err[5];   // large-displacement check: violation flag
     out[11] = m;        // tiled list: largest staged neighbourhood of a tile
-    int32_t stop = 0;
-    if (g.gate) {
-        stop = ((flags[0] & 1) != 0 || (g.fold && energy[4] > g.thr2)) ? 1 : 0;
-        g.gate[0] = stop;
-    }
-    out[12] = g.idx;
+    const int32_t stop = step && ((flags[0] & 1) != 0 || (fold && energy[4] > g.run.thr2)) ? 1 : 0;
+    out[12] = ran;
     out[13] = stop;
+    if (step) g.run.gate[0] = folded ? 0 : stop;
 }
 
 hipError_t launch_gather_flags(const int64_t* status, const int64_t* err, const int64_t* flags, double* energy,

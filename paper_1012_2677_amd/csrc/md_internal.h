@@ -63,9 +63,10 @@ constexpr int kTileMaxSlots = 256;
 // the maximum over the slots.
 constexpr int kMaxSlots = 256;
 constexpr int kMaxSlotStride = 8;   // int64 words between slots
-__host__ __device__ inline unsigned long long* max_slot(unsigned long long* base, int64_t blk)
+__host__ __device__ inline unsigned long long* max_slot(unsigned long long* base, int64_t blk,
+                                                        int slots = kMaxSlots)
 {
-    return base + (blk & (kMaxSlots - 1)) * kMaxSlotStride;
+    return base + (blk & (slots - 1)) * kMaxSlotStride;
 }
 
 __host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -290,6 +291,70 @@ __device__ __forceinline__ double rcp64_1(double x)
 }
 
 // ---------------------------------------------------------------------------
+// Runs of queued steps (half-skin rule): a step that finds the list expired
+// (largest squared displacement > thr2), or a force not finite, must not run, nor
+// may those queued after it.  Two ways of telling them:
+//   by a gate: a pass of its own after each step (k_gather_flags) reads the
+//     maxima and sets a word that the passes after it look at first;
+//   folded (few blocks): the force pass of step b puts its block maxima of the
+//     squared displacement (word 0 of a slot) and a mark of non-finite forces
+//     (word 1) into set b % 3 of kRunSlots slots; the passes of step b + 1 read
+//     that set and decide for themselves, alike, and the first wave records a
+//     stop for the passes after them (gate[0] = 1, gate[1] = the steps that
+//     ran) or clears set (b + 2) % 3, last read by step b.
+// The fold saves a launch and its 3.4 to 6 us per step (4,000 particles FP64,
+// 100 steps: 3.11 to 2.63 ms per call, tiles as they are) and adds the wait
+// for 17 lines to the start of every block: 3 to 4% of a pass of many tiles
+// (32M mixed 2.31 to 2.39 ms, 4M FP64 434 to 441 us), hence kFoldBlocks.
+// ---------------------------------------------------------------------------
+constexpr int64_t kFoldBlocks = 8192;
+constexpr int kRunSlots = 16;       // one cache line each, which every deciding wave reads
+static_assert(3 * kRunSlots <= kMaxSlots, "the three sets share the maxima slots");
+struct RunIo {
+    unsigned long long* slots = nullptr;   // the three sets (nullptr: not in a run)
+    int32_t* gate = nullptr;               // [0] stopped, [1] steps that ran
+    int32_t idx = 0;                       // the step's place in the run
+    double thr2 = 0.0;
+};
+__host__ __device__ inline unsigned long long* run_set(const RunIo& r, int idx)
+{
+    return r.slots + (int64_t)(idx % 3) * kRunSlots * kMaxSlotStride;
+}
+// What a wave has to read for its decision (issue early, decide late).
+struct RunCheck {
+    unsigned long long d2 = 0, bad = 0;
+    int32_t stopped = 0;
+};
+__device__ __forceinline__ RunCheck run_check_load(const RunIo& r)
+{
+    RunCheck c;
+    if (r.idx > 0) {
+        const ulonglong2 v =
+            *(const ulonglong2*)(run_set(r, r.idx - 1) + (lane_id() & (kRunSlots - 1)) * kMaxSlotStride);
+        c.d2 = v.x;
+        c.bad = v.y;
+        c.stopped = r.gate[0];
+    }
+    return c;
+}
+__device__ __forceinline__ bool run_stopped(const RunIo& r, const RunCheck& c)
+{
+    return __ballot(__longlong_as_double((long long)c.d2) > r.thr2 || c.bad != 0 || c.stopped != 0) != 0;
+}
+// The first wave's part (one wave of the whole launch).
+__device__ __forceinline__ void run_mark(const RunIo& r, const RunCheck& c, bool stop)
+{
+    if (stop) {
+        if (lane_id() == 0 && c.stopped == 0) {
+            r.gate[1] = r.idx;
+            r.gate[0] = 1;
+        }
+    } else if (lane_id() < kRunSlots) {
+        *(ulonglong2*)(run_set(r, r.idx + 1) + lane_id() * kMaxSlotStride) = make_ulonglong2(0ull, 0ull);
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Launchers (each returns hipGetLastError() of its launches)
 // ---------------------------------------------------------------------------
 // md_cells.hip
@@ -302,9 +367,9 @@ hipError_t launch_resort(const Geo& g, const int32_t* order, const double* pos, 
                          hipStream_t s);
 hipError_t launch_pack(const Geo& g, const double* q, double* pos, hipStream_t s);
 // frame[id[slot]] = pos[slot] (double4, w = 0): positions in the original order
-// (nothing when gate is given and *gate != 0)
+// (nothing when the run has stopped)
 hipError_t launch_record(const Geo& g, const double* pos, const int32_t* id, double* frame, hipStream_t s,
-                         const int32_t* gate = nullptr);
+                         const RunIo& run = RunIo());
 hipError_t launch_ref_copy(const Geo& g, const double* pos, const int32_t* cell_xyz, double* pos_ref,
                            float* pos32, hipStream_t s);
 
@@ -359,7 +424,7 @@ struct StepIo {
     bool drift;
     bool track_speed;             // also record the largest squared drift speed
     TileIo tile;                  // tiled list (tile.stage > 0)
-    const int32_t* gate = nullptr;  // full list: the pass does nothing when *gate != 0
+    RunIo run;                    // full list: the step's run of queued steps (run.gate: given from step 1 on by a gate)
 };
 hipError_t launch_force_step(const Geo& g, const LJ& lj, int precision, const StepIo& io, hipStream_t s);
 int64_t pair_blocks(const Geo& g);   // blocks (and energy partials) of one pair-kernel launch
@@ -393,18 +458,15 @@ hipError_t launch_reduce_energy(const double* part_pw, int64_t nbf, const double
                                 const int32_t* gate = nullptr);
 hipError_t launch_reduce_pair(const double* part, int64_t nb, double scale0, double scale1,
                               double* out2, hipStream_t s, bool accumulate = false);
-// The step decision of a run of steps queued without reading flags back
-// (half-skin rule): the gather that follows step idx - 1 of the run sets *gate
-// when step idx must rebuild first (largest squared displacement > thr2) or a
-// non-finite force was seen; the passes of later steps, given the gate, then
-// do nothing, and the gathers after it keep out as the stopping one wrote it.
-// out[12] = idx and out[13] = 1 when it stopped the run.
+// A gather in a run of queued steps: out[12] = the steps that ran, out[13] = 1 when
+// the next one must rebuild first or a force was not finite.  By a gate: after
+// every step idx, setting run.gate[0] when it stopped the run (the gathers after
+// it then leave out as the stopping one wrote it).  Folded (run.slots): once at
+// the run's end, idx the steps queued; clears the run's slots and gate.  drift:
+// step idx ends with a drift (all but the last of a call).
 struct FlagGate {
-    int32_t* gate = nullptr;      // nullptr: a plain gather
-    double thr2 = 0.0;
-    int32_t idx = 0;
-    bool fold = true;             // fold the slot maxima into energy[4], energy[5]
-    bool clear = false;           // and clear the slots after reading them
+    RunIo run;                    // run.gate nullptr: a plain gather
+    bool drift = false;
 };
 // Also folds the slot maxima of d2 and v2 (mx) into energy[4] and energy[5].
 hipError_t launch_gather_flags(const int64_t* status, const int64_t* err, const int64_t* flags, double* energy,
