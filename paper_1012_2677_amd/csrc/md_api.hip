@@ -371,7 +371,10 @@ int md_bin_cells(const md_params* p, const double* pos, md_cells* cells, void* w
     if ((rc = check_ws(c, ws, ws_bytes)) != MD_OK) return rc;
     for (int k = 0; k < 3; ++k) cells->ncell[k] = c.nc[k];
     int64_t* err = (int64_t*)((char*)ws + c.W.scal);
-    MD_HIP(launch_fill_i32((int32_t*)err, 0, 2, stream), "md_bin_cells/clear");
+    ClearList clear;
+    clear.add(err, 2);
+    if (bin_clears_counts(c.g)) clear.add(cells->count, c.g.ncell);
+    MD_HIP(launch_clear(clear, stream), "md_bin_cells/clear");
     MD_HIP(launch_bin(c.g, pos, *cells, ws, c.W, err, stream), "md_bin_cells");
     cells->sorted = 0;
     return MD_OK;
@@ -388,7 +391,10 @@ int md_build_pairlist(const md_params* p, const double* pos, const md_cells* cel
     if ((rc = check_list(c, list)) != MD_OK) return rc;
     if ((rc = check_ws(c, ws, ws_bytes)) != MD_OK) return rc;
     const bool half = p->list_layout == MD_LIST_HALF;
-    MD_HIP(launch_build(c.g, p->rs, pos, *cells, *list, ws, c.W, false, half, nullptr, MD_BUILD_AUTO, stream),
+    ClearList clear;
+    build_clears(c.g, *list, ws, c.W, false, nullptr, clear);
+    MD_HIP(launch_clear(clear, stream), "md_build_pairlist/clear");
+    MD_HIP(launch_build(c.g, p->rs, pos, *cells, *list, ws, c.W, false, half, nullptr, MD_BUILD_AUTO, nullptr, stream),
            "md_build_pairlist");
     list->tiled = 0;
     list->half = half ? 1 : 0;
@@ -576,7 +582,8 @@ static int check_state(const Ctx& c, const md_params* p, md_state* st)
 }
 
 // bin + optional re-sort + reference copy + list build (no wait)
-static int read_flags(const Ctx& c, md_state* st, hipStream_t s, int64_t out[16]);
+static int read_flags(const Ctx& c, md_state* st, hipStream_t s, int64_t out[16], bool gathered = false);
+static GatherIo gather_io(const Ctx& c, md_state* st);
 
 // slot arrays of the block maxima of d2 (which = 0) and v2 (which = 1)
 static unsigned long long* mx_slots(const Ctx& c, md_state* st, int which)
@@ -592,7 +599,7 @@ static hipError_t clear_maxima(const Ctx& c, md_state* st, hipStream_t s)
 // Pair list of the state: tiled (16-bit entries into each tile's staged
 // neighbourhood) when the geometry has tiles and the slots are in cell order,
 // else slot entries.
-static int build_list(const Ctx& c, const md_params* p, md_state* st, bool tiled, Timer& T, hipStream_t s)
+static int build_list(const Ctx& c, const md_params* p, md_state* st, bool tiled, bool cleared, Timer& T, hipStream_t s)
 {
     if (st->list.capacity < list_words(c, &st->list, tiled)) {
         // the caller gave room for 16-bit entries only; slot entries need twice
@@ -601,12 +608,17 @@ static int build_list(const Ctx& c, const md_params* p, md_state* st, bool tiled
         return fail(MD_ERR_CAPACITY, "slot entries need %lld words of nbr, capacity is %lld",
                     (long long)list_words(c, &st->list, tiled), (long long)st->list.capacity);
     }
-    int64_t* tmax = (int64_t*)((char*)st->ws + c.W.tmax);
-    if (tiled) MD_HIP(launch_fill_i32((int32_t*)tmax, 0, 2 * kTileMaxSlots, s), "rebuild/tile-max");
+    unsigned long long* tmax = (unsigned long long*)((char*)st->ws + c.W.tmax);
     tick(T, MD_T_BUILD, 0, s);
+    if (!cleared) {
+        ClearList clear;
+        build_clears(c.g, st->list, st->ws, c.W, tiled, tmax, clear);
+        MD_HIP(launch_clear(clear, s), "rebuild/clear");
+    }
     const bool half = p->list_layout == MD_LIST_HALF;
-    MD_HIP(launch_build(c.g, p->rs, st->pos, st->cells, st->list, st->ws, c.W, tiled, half,
-                        (unsigned long long*)tmax, p->build_waves, s),
+    const GatherIo gather = gather_io(c, st);
+    MD_HIP(launch_build(c.g, p->rs, st->pos, st->cells, st->list, st->ws, c.W, tiled, half, tmax, p->build_waves, &gather,
+                        s),
            "rebuild/build");
     tick(T, MD_T_BUILD, 1, s);
     st->list_tiled = tiled ? 1 : 0;
@@ -624,12 +636,19 @@ static int rebuild(const Ctx& c, const md_params* p, md_state* st, bool allow_re
                    hipStream_t s, int64_t f[16])
 {
     int64_t* err = (int64_t*)((char*)st->ws + c.W.scal);
+    const bool resort = allow_resort && p->resort_every > 0 && (st->rebuilds % p->resort_every) == 0;
+    // tiled rows start at even entries of 4-byte aligned cell blocks
+    const bool tiled = c.g.tc > 0 && resort && (st->list.cell_stride & 1) == 0;
     tick(T, MD_T_BIN, 0, s);
+    // what the passes below count into, in one launch
+    ClearList clear;
+    if (bin_clears_counts(c.g)) clear.add(st->cells.count, c.g.ncell);
+    build_clears(c.g, st->list, st->ws, c.W, tiled, (unsigned long long*)((char*)st->ws + c.W.tmax), clear);
+    MD_HIP(launch_clear(clear, s), "rebuild/clear");
     MD_HIP(launch_bin(c.g, st->pos, st->cells, st->ws, c.W, err, s), "rebuild/bin");
     tick(T, MD_T_BIN, 1, s);
     for (int k = 0; k < 3; ++k) st->cells.ncell[k] = c.nc[k];
     st->cells.sorted = 0;
-    const bool resort = allow_resort && p->resort_every > 0 && (st->rebuilds % p->resort_every) == 0;
     if (resort) {
         tick(T, MD_T_RESORT, 0, s);
         MD_HIP(launch_resort(c.g, st->cells.order, st->pos, st->vel, st->id, st->pos_alt, st->vel_alt,
@@ -647,16 +666,14 @@ static int rebuild(const Ctx& c, const md_params* p, md_state* st, bool allow_re
                                p->precision == MD_MIXED ? st->pos32 : nullptr, s),
                "rebuild/ref");
     }
-    // tiled rows start at even entries of 4-byte aligned cell blocks
-    const bool tiled = c.g.tc > 0 && st->cells.sorted && (st->list.cell_stride & 1) == 0;
-    int rc = build_list(c, p, st, tiled, T, s);
+    int rc = build_list(c, p, st, tiled, true, T, s);
     if (rc != MD_OK) return rc;
-    if ((rc = read_flags(c, st, s, f)) != MD_OK) return rc;
+    if ((rc = read_flags(c, st, s, f, true)) != MD_OK) return rc;
     if (st->list_tiled) {
         if (f[11] > tile_stage_cap(p->precision)) {
             timer_collect(T);
-            if ((rc = build_list(c, p, st, false, T, s)) != MD_OK) return rc;
-            if ((rc = read_flags(c, st, s, f)) != MD_OK) return rc;
+            if ((rc = build_list(c, p, st, false, false, T, s)) != MD_OK) return rc;
+            if ((rc = read_flags(c, st, s, f, true)) != MD_OK) return rc;
         } else {
             st->tile_stage = (int32_t)f[11];
         }
@@ -677,14 +694,20 @@ static TileIo tile_io(const md_state* st)
     return t;
 }
 
-// wait for the stream and read, in one copy: list status [0..3], cell-grid
-// error flags [4..5], force flags [6], max squared displacement bits [7]
-static int read_flags(const Ctx& c, md_state* st, hipStream_t s, int64_t out[16])
+static GatherIo gather_io(const Ctx& c, md_state* st)
 {
     int64_t* scal = (int64_t*)((char*)st->ws + c.W.scal);
-    MD_HIP(launch_gather_flags(st->list.status, scal, st->flags, st->energy, (const int64_t*)((char*)st->ws + c.W.tmax),
-                               mx_slots(c, st, 0), scal + kScalOut, s),
-           "flags/gather");
+    return {scal, st->flags, st->energy, (const int64_t*)((char*)st->ws + c.W.tmax), mx_slots(c, st, 0),
+            scal + kScalOut};
+}
+
+// wait for the stream and read, in one copy (of what the list build gathered,
+// else gathered here): list status [0..3], cell-grid
+// error flags [4..5], force flags [6], max squared displacement bits [7]
+static int read_flags(const Ctx& c, md_state* st, hipStream_t s, int64_t out[16], bool gathered)
+{
+    int64_t* scal = (int64_t*)((char*)st->ws + c.W.scal);
+    if (!gathered) MD_HIP(launch_gather_flags(st->list.status, gather_io(c, st), s), "flags/gather");
     int64_t local[16];
     int64_t* dst = st->host_scratch ? st->host_scratch : local;
     MD_HIP(hipMemcpyAsync(dst, scal + kScalOut, 16 * sizeof(int64_t), hipMemcpyDeviceToHost, s), "flags/copy");
@@ -1013,9 +1036,7 @@ static int step_runs(const Ctx& c, const md_params* p, md_state* st, int64_t nst
             if (!folded || b + 1 == run) {
                 fg.run.idx = (int32_t)(b + 1);
                 fg.drift = !last;     // the last step of a call has no drift
-                MD_HIP(launch_gather_flags(st->list.status, scal, st->flags, st->energy,
-                                           (const int64_t*)((char*)st->ws + c.W.tmax), mx_slots(c, st, 0),
-                                           scal + kScalOut, s, fg),
+                MD_HIP(launch_gather_flags(st->list.status, gather_io(c, st), s, fg),
                        "step/gather");
             }
         }

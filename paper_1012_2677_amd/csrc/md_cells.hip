@@ -1,12 +1,15 @@
 // Cell grid and re-sort kernels (Sec. 2.2 GridList, Sec. 3.3 re-sort).
 //
 // GridList on the GPU: a thread per slot labels it with its cell and takes a
-// rank inside the cell with an integer atomic; a three-phase scan turns the
-// per-cell counts into pointers; ranks place the slots; finally every cell's
-// segment is sorted by slot, which makes the result identical to the
-// sequential counting sort that visits particles in index order (stable).
+// rank inside the cell with an integer atomic; a scan turns the
+// per-cell counts into pointers; ranks place the slots; finally each slot
+// counts the smaller ones of its cell, whose number is its stable place, which
+// makes the result identical to the
+// sequential counting sort that visits particles in index order.
 // All passes are integer work and read/write each array once, so they are
 // bound by HBM bandwidth.
+
+#include <type_traits>
 
 #include "md_internal.h"
 
@@ -23,6 +26,28 @@ hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t count, hipStream_t s)
     if (count <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_fill_i32, dim3((unsigned)ceil_div(count, kStreamBlock)), dim3(kStreamBlock),
                        0, s, p, v, count);
+    return hipGetLastError();
+}
+
+// Several arrays cleared in one launch.
+__global__ __launch_bounds__(kStreamBlock) void k_clear(ClearList l)
+{
+    int64_t i = (int64_t)blockIdx.x * kStreamBlock + threadIdx.x;
+    for (int k = 0; k < ClearList::kMost; ++k) {
+        if (i < l.words[k]) {
+            l.p[k][i] = 0;
+            return;
+        }
+        i -= l.words[k];
+    }
+}
+
+hipError_t launch_clear(const ClearList& l, hipStream_t s)
+{
+    int64_t total = 0;
+    for (int k = 0; k < ClearList::kMost; ++k) total += l.words[k];
+    if (total == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_clear, dim3((unsigned)ceil_div(total, kStreamBlock)), dim3(kStreamBlock), 0, s, l);
     return hipGetLastError();
 }
 
@@ -150,6 +175,50 @@ __global__ __launch_bounds__(kStreamBlock) void k_scan_final(const int32_t* __re
     if (blockIdx.x == 0 && threadIdx.x == 0) out[m] = bsum[nb];
 }
 
+// The same scan in one launch of one block, for grids whose counts one block
+// reads in one turn (3375 cells: 4.5 us against three launches and their gaps;
+// 28^3 cells in three turns 22 us, three launches 13).
+constexpr int kScanOneThreads = 1024;
+constexpr int kScanOneItems = 8;              // per thread and turn
+constexpr int64_t kScanOneCells = kScanOneThreads * kScanOneItems;
+__global__ __launch_bounds__(kScanOneThreads) void k_scan_one(const int32_t* __restrict__ in, int m,
+                                                              int32_t* __restrict__ out)
+{
+    __shared__ int32_t s_wave[kScanOneThreads / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int32_t carry = 0;
+    for (int t0 = 0; t0 < m; t0 += kScanOneThreads * kScanOneItems) {
+        const int base = t0 + (int)threadIdx.x * kScanOneItems;
+        int32_t v[kScanOneItems], sum = 0;
+#pragma unroll
+        for (int k = 0; k < kScanOneItems; ++k) v[k] = base + k < m ? in[base + k] : 0;
+#pragma unroll
+        for (int k = 0; k < kScanOneItems; ++k) sum += v[k];
+        int32_t x = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int32_t y = __shfl_up(x, o, 64);
+            if (lane >= o) x += y;
+        }
+        if (lane == 63) s_wave[wave] = x;
+        __syncthreads();
+        int32_t run = carry + x - sum, tot = 0;
+        for (int w = 0; w < kScanOneThreads / 64; ++w) {
+            const int32_t t = s_wave[w];
+            if (w < wave) run += t;
+            tot += t;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kScanOneItems; ++k) {
+            if (base + k < m) out[base + k] = run;
+            run += v[k];
+        }
+        carry += tot;
+    }
+    if (threadIdx.x == 0) out[m] = carry;
+}
+
 // ---- place + per-cell sort ---------------------------------------------------
 __global__ __launch_bounds__(kStreamBlock) void k_scatter(int64_t n, const int32_t* __restrict__ cell_of,
                                                           const int32_t* __restrict__ rank,
@@ -161,13 +230,17 @@ __global__ __launch_bounds__(kStreamBlock) void k_scatter(int64_t n, const int32
     order[start[cell_of[i]] + rank[i]] = (int32_t)i;
 }
 
-// Insertion sort of each cell's segment by slot (segments hold ~11 slots at
-// rho = 0.5; any length is handled).
-// Insertion sort of each cell's slots (the scatter leaves the groups of
-// different waves in atomic order).  A block's cells are contiguous in
-// `order`: when their slots fit, they are loaded into LDS with coalesced
-// loads, sorted there (one thread per cell) and written back; otherwise each
-// thread sorts its cell in place in global memory.
+// Stable order of each cell's slots (the scatter leaves the groups of different
+// waves in atomic order).  The cells of a block, CELLS of them, are
+// contiguous in `order`: when their slots fit, they are loaded into LDS, and
+// each slot's place in its cell is the number of smaller ones in it (a thread
+// per slot, ~11 reads each at rho = 0.5); otherwise a thread per cell sorts
+// its cell in place in global memory.  Few cells per block on small grids, which
+// otherwise have too few blocks (28^3 cells at 11.7 particles, 64, 32, 16, 8 per
+// block: 6.4, 5.1, 4.1, 5.7 us; an insertion sort by a thread per cell of 256
+// 17.5), more on large ones, where a block's three waits cost more (142^3 cells:
+// 16, 32, 64 per block 211, 167, 127 us; the insertion sort 117).
+constexpr int64_t kSortFewCells = 131072;
 constexpr int kSortLds = 4096;   // slots of one block's cells sorted in LDS
 
 __device__ __forceinline__ void insertion_sort(int32_t* v, int32_t len)
@@ -183,61 +256,95 @@ __device__ __forceinline__ void insertion_sort(int32_t* v, int32_t len)
     }
 }
 
+template <int CELLS>
 __global__ __launch_bounds__(kStreamBlock) void k_sort_cells(int64_t ncell, const int32_t* __restrict__ start,
                                                              int32_t* __restrict__ order)
 {
     __shared__ int32_t s_o[kSortLds];
-    const int64_t c0 = (int64_t)blockIdx.x * blockDim.x;
-    const int64_t c1 = c0 + blockDim.x < ncell ? c0 + blockDim.x : ncell;
-    const int64_t c = c0 + threadIdx.x;
-    const int32_t b0 = start[c0], b1 = start[c1];
-    if (b1 - b0 <= kSortLds) {
-        for (int32_t t = threadIdx.x; t < b1 - b0; t += blockDim.x) s_o[t] = order[b0 + t];
-        __syncthreads();
-        if (c < c1) insertion_sort(s_o + (start[c] - b0), start[c + 1] - start[c]);
-        __syncthreads();
-        for (int32_t t = threadIdx.x; t < b1 - b0; t += blockDim.x) order[b0 + t] = s_o[t];
-    } else if (c < c1) {
-        insertion_sort(order + start[c], start[c + 1] - start[c]);
+    __shared__ uint8_t s_c[kSortLds];
+    __shared__ int32_t s_start[CELLS + 1];
+    const int64_t c0 = (int64_t)blockIdx.x * CELLS;
+    const int nc = (int)(c0 + CELLS < ncell ? CELLS : ncell - c0);
+    const int tid = threadIdx.x;
+    if (tid <= nc) s_start[tid] = start[c0 + tid];
+    __syncthreads();
+    const int32_t b0 = s_start[0], len = s_start[nc] - b0;
+    if (len > kSortLds) {
+        if (tid < nc) insertion_sort(order + s_start[tid], s_start[tid + 1] - s_start[tid]);
+        return;
+    }
+    for (int t = tid; t < len; t += kStreamBlock) s_o[t] = order[b0 + t];
+    // kMark threads per cell mark its slots
+    constexpr int kMark = kStreamBlock / CELLS;
+    const int cm = tid / kMark;
+    if (cm < nc)
+        for (int t = s_start[cm] - b0 + tid % kMark; t < s_start[cm + 1] - b0; t += kMark) s_c[t] = (uint8_t)cm;
+    __syncthreads();
+    for (int t = tid; t < len; t += kStreamBlock) {
+        const int32_t x = s_o[t];
+        const int c = s_c[t], q0 = s_start[c] - b0, q1 = s_start[c + 1] - b0;
+        int r = 0;
+        for (int q = q0; q < q1; ++q) r += s_o[q] < x;
+        order[b0 + q0 + r] = x;
     }
 }
 
 // ---- the same for small systems in one block --------------------------------
-// Label, count (LDS atomics), exclusive scan, place and per-cell sort in one
-// launch of one block: the same count, start, cell_of, cell_xyz and (sorted)
-// order as the kernels above, without their seven launches, which dominate
-// a rebuild of a few thousand particles.
+// Label, count (LDS atomics), exclusive scan, place and the stable order in one
+// launch of one block: the same count, start, cell_of, cell_xyz and
+// order as the kernels above, without their launches, which dominate
+// a rebuild of a few thousand particles.  Cells and ranks stay in registers, the
+// unsorted order in LDS.  (4,000 particles: 23 us with ranks and order in global
+// memory and an insertion sort there, 8 here; beyond kBinSmallN one compute
+// unit is too few: 62,000 particles took 196 us so.)
 constexpr int kBinSmallThreads = 1024;
-constexpr int64_t kBinSmallN = 65536;
+constexpr int64_t kBinSmallN = 16384;
 constexpr int64_t kBinSmallCells = 4096;
 
+template <int ITEMS>
 __global__ __launch_bounds__(kBinSmallThreads) void k_bin_small(Geo g, const double4* __restrict__ pos,
                                                                 int32_t* __restrict__ cell_of,
                                                                 int32_t* __restrict__ cell_xyz,
                                                                 int32_t* __restrict__ count,
                                                                 int32_t* __restrict__ start,
                                                                 int32_t* __restrict__ order,
-                                                                int32_t* __restrict__ rank,
                                                                 int64_t* __restrict__ err)
 {
-    __shared__ int32_t s_cnt[kBinSmallCells];
+    static_assert(kBinSmallCells <= 4096 && ITEMS * kBinSmallThreads <= 65536, "cell and rank share a word");
+    __shared__ int32_t s_cnt[kBinSmallCells + 1];
     __shared__ int32_t s_wave[kBinSmallThreads / 64];
+    __shared__ uint16_t s_ord[ITEMS * kBinSmallThreads];
     const int tid = threadIdx.x;
     const int nc = (int)g.ncell;
     const int n = (int)g.n;
     for (int c = tid; c < nc; c += kBinSmallThreads) s_cnt[c] = 0;
     __syncthreads();
     bool outside = false;
-    for (int i = tid; i < n; i += kBinSmallThreads) {
-        const double4 p = pos[i];
-        outside |= !(p.x >= 0.0 && p.x < g.L[0] && p.y >= 0.0 && p.y < g.L[1] && p.z >= 0.0 && p.z < g.L[2]);
-        const int cx = cell_coord(p.x, g.inv[0], g.nc[0]);
-        const int cy = cell_coord(p.y, g.inv[1], g.nc[1]);
-        const int cz = cell_coord(p.z, g.inv[2], g.nc[2]);
-        const int32_t c = (cx * g.nc[1] + cy) * g.nc[2] + cz;
-        cell_of[i] = c;
-        cell_xyz[i] = cx | (cy << 10) | (cz << 20);
-        rank[i] = atomicAdd(&s_cnt[c], 1);
+    uint32_t item[ITEMS];     // cell | rank << 12
+    constexpr int B = 4;      // positions in flight per thread
+#pragma unroll
+    for (int k0 = 0; k0 < ITEMS; k0 += B) {
+        double4 p[B];
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            const int i = tid + (k0 + k) * kBinSmallThreads;
+            p[k] = pos[i < n ? i : n - 1];
+        }
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            const int i = tid + (k0 + k) * kBinSmallThreads;
+            item[k0 + k] = 0;
+            if (i >= n) continue;
+            outside |= !(p[k].x >= 0.0 && p[k].x < g.L[0] && p[k].y >= 0.0 && p[k].y < g.L[1] && p[k].z >= 0.0 &&
+                         p[k].z < g.L[2]);
+            const int cx = cell_coord(p[k].x, g.inv[0], g.nc[0]);
+            const int cy = cell_coord(p[k].y, g.inv[1], g.nc[1]);
+            const int cz = cell_coord(p[k].z, g.inv[2], g.nc[2]);
+            const int32_t c = (cx * g.nc[1] + cy) * g.nc[2] + cz;
+            cell_of[i] = c;
+            cell_xyz[i] = cx | (cy << 10) | (cz << 20);
+            item[k0 + k] = (uint32_t)c | (uint32_t)atomicAdd(&s_cnt[c], 1) << 12;
+        }
     }
     if (outside) atomicOr((unsigned long long*)err, 2ull);
     __syncthreads();
@@ -258,7 +365,6 @@ __global__ __launch_bounds__(kBinSmallThreads) void k_bin_small(Geo g, const dou
     __syncthreads();
     int32_t base = x - run;
     for (int w2 = 0; w2 < wave; ++w2) base += s_wave[w2];
-    __syncthreads();
     for (int c = c0; c < c1; ++c) {
         const int32_t v = s_cnt[c];
         count[c] = v;
@@ -266,12 +372,29 @@ __global__ __launch_bounds__(kBinSmallThreads) void k_bin_small(Geo g, const dou
         s_cnt[c] = base;
         base += v;
     }
-    if (tid == 0) start[nc] = n;
+    if (tid == 0) {
+        start[nc] = n;
+        s_cnt[nc] = n;
+    }
     __syncthreads();
-    for (int i = tid; i < n; i += kBinSmallThreads) order[s_cnt[cell_of[i]] + rank[i]] = i;
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const int i = tid + k * kBinSmallThreads;
+        if (i < n) s_ord[s_cnt[item[k] & 4095u] + (int)(item[k] >> 12)] = (uint16_t)i;
+    }
     __syncthreads();
-    for (int c = tid; c < nc; c += kBinSmallThreads) insertion_sort(order + start[c], count[c]);
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const int i = tid + k * kBinSmallThreads;
+        if (i >= n) continue;
+        const int q0 = s_cnt[item[k] & 4095u], q1 = s_cnt[(item[k] & 4095u) + 1];
+        int r = 0;
+        for (int q = q0; q < q1; ++q) r += (int)s_ord[q] < i;
+        order[q0 + r] = i;
+    }
 }
+
+bool bin_clears_counts(const Geo& g) { return !(g.n <= kBinSmallN && g.ncell <= kBinSmallCells); }
 
 hipError_t launch_bin(const Geo& g, const double* pos, const md_cells& cells, void* ws,
                       const WsLayout& L, int64_t* err_flags, hipStream_t s)
@@ -279,27 +402,39 @@ hipError_t launch_bin(const Geo& g, const double* pos, const md_cells& cells, vo
     char* w = (char*)ws;
     int32_t* rank = (int32_t*)(w + L.rank);
     int32_t* bsum = (int32_t*)(w + L.bsum);
-    if (g.n <= kBinSmallN && g.ncell <= kBinSmallCells) {
-        hipLaunchKernelGGL(k_bin_small, dim3(1), dim3(kBinSmallThreads), 0, s, g, (const double4*)pos,
-                           cells.cell_of, cells.cell_xyz, cells.count, cells.start, cells.order, rank, err_flags);
+    if (!bin_clears_counts(g)) {
+        if (g.n <= 4 * kBinSmallThreads)
+            hipLaunchKernelGGL((k_bin_small<4>), dim3(1), dim3(kBinSmallThreads), 0, s, g, (const double4*)pos,
+                               cells.cell_of, cells.cell_xyz, cells.count, cells.start, cells.order, err_flags);
+        else
+            hipLaunchKernelGGL((k_bin_small<16>), dim3(1), dim3(kBinSmallThreads), 0, s, g, (const double4*)pos,
+                               cells.cell_of, cells.cell_xyz, cells.count, cells.start, cells.order, err_flags);
         return hipGetLastError();
     }
-    hipError_t e = launch_fill_i32(cells.count, 0, g.ncell, s);
-    if (e != hipSuccess) return e;
     const unsigned nbn = (unsigned)ceil_div(g.n, kStreamBlock);
     hipLaunchKernelGGL(k_label, dim3(nbn), dim3(kStreamBlock), 0, s, g, (const double4*)pos,
                        cells.cell_of, cells.cell_xyz, cells.count, rank, err_flags);
-    const int64_t nbs = ceil_div(g.ncell, kScanItems);
-    hipLaunchKernelGGL(k_scan_partial, dim3((unsigned)nbs), dim3(kStreamBlock), 0, s,
-                       (const int32_t*)cells.count, g.ncell, bsum);
-    hipLaunchKernelGGL(k_scan_bsums, dim3(1), dim3(kStreamBlock), 0, s, bsum, nbs);
-    hipLaunchKernelGGL(k_scan_final, dim3((unsigned)nbs), dim3(kStreamBlock), 0, s,
-                       (const int32_t*)cells.count, g.ncell, (const int32_t*)bsum, nbs, cells.start);
+    if (g.ncell <= kScanOneCells) {
+        hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kScanOneThreads), 0, s, (const int32_t*)cells.count, (int)g.ncell,
+                           cells.start);
+    } else {
+        const int64_t nbs = ceil_div(g.ncell, kScanItems);
+        hipLaunchKernelGGL(k_scan_partial, dim3((unsigned)nbs), dim3(kStreamBlock), 0, s,
+                           (const int32_t*)cells.count, g.ncell, bsum);
+        hipLaunchKernelGGL(k_scan_bsums, dim3(1), dim3(kStreamBlock), 0, s, bsum, nbs);
+        hipLaunchKernelGGL(k_scan_final, dim3((unsigned)nbs), dim3(kStreamBlock), 0, s,
+                           (const int32_t*)cells.count, g.ncell, (const int32_t*)bsum, nbs, cells.start);
+    }
     hipLaunchKernelGGL(k_scatter, dim3(nbn), dim3(kStreamBlock), 0, s, g.n,
                        (const int32_t*)cells.cell_of, (const int32_t*)rank,
                        (const int32_t*)cells.start, cells.order);
-    hipLaunchKernelGGL(k_sort_cells, dim3((unsigned)ceil_div(g.ncell, kStreamBlock)), dim3(kStreamBlock),
-                       0, s, g.ncell, (const int32_t*)cells.start, cells.order);
+    auto sort = [&](auto cells_per_block) {
+        constexpr int CELLS = decltype(cells_per_block)::value;
+        hipLaunchKernelGGL((k_sort_cells<CELLS>), dim3((unsigned)ceil_div(g.ncell, CELLS)), dim3(kStreamBlock), 0, s,
+                           g.ncell, (const int32_t*)cells.start, cells.order);
+    };
+    if (g.ncell <= kSortFewCells) sort(std::integral_constant<int, 16>());
+    else sort(std::integral_constant<int, 128>());
     return hipGetLastError();
 }
 

@@ -264,92 +264,14 @@ hipError_t launch_reduce_pair(const double* part, int64_t nb, double scale0, dou
     return hipGetLastError();
 }
 
-// status[0] = total entries, status[1] = largest cell block (stride needed):
-// per-block (sum, max) partials, then one block combines them in order.
-constexpr int kStatsBlocks = 1024;
-
-__global__ __launch_bounds__(kStreamBlock) void k_rows_partial(const int32_t* __restrict__ rows, int64_t ncell,
-                                                               long long* __restrict__ part)
-{
-    __shared__ long long s_sum[kStreamBlock / 64], s_max[kStreamBlock / 64];
-    long long sum = 0, mx = 0;
-    for (int64_t c = (int64_t)blockIdx.x * kStreamBlock + threadIdx.x; c < ncell;
-         c += (int64_t)gridDim.x * kStreamBlock) {
-        const long long r = rows[c];
-        sum += r;
-        mx = r > mx ? r : mx;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        sum += __shfl_xor(sum, o, 64);
-        const long long y = __shfl_xor(mx, o, 64);
-        mx = y > mx ? y : mx;
-    }
-    if ((threadIdx.x & 63) == 0) {
-        s_sum[threadIdx.x >> 6] = sum;
-        s_max[threadIdx.x >> 6] = mx;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        long long ts = 0, tm = 0;
-        for (int w = 0; w < kStreamBlock / 64; ++w) {
-            ts += s_sum[w];
-            tm = s_max[w] > tm ? s_max[w] : tm;
-        }
-        part[2 * blockIdx.x] = ts;
-        part[2 * blockIdx.x + 1] = tm;
-    }
-}
-
-__global__ __launch_bounds__(kStatsBlocks) void k_rows_final(const long long* __restrict__ part, int nb,
-                                                             int64_t* __restrict__ status)
-{
-    __shared__ long long s_sum[kStatsBlocks / 64], s_max[kStatsBlocks / 64];
-    long long sum = 0, mx = 0;
-    if ((int)threadIdx.x < nb) {
-        sum = part[2 * threadIdx.x];
-        mx = part[2 * threadIdx.x + 1];
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        sum += __shfl_xor(sum, o, 64);
-        const long long y = __shfl_xor(mx, o, 64);
-        mx = y > mx ? y : mx;
-    }
-    if ((threadIdx.x & 63) == 0) {
-        s_sum[threadIdx.x >> 6] = sum;
-        s_max[threadIdx.x >> 6] = mx;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        long long ts = 0, tm = 0;
-        for (int w = 0; w < kStatsBlocks / 64; ++w) {
-            ts += s_sum[w];
-            tm = s_max[w] > tm ? s_max[w] : tm;
-        }
-        status[0] = ts;
-        status[1] = tm;
-    }
-}
-
-hipError_t launch_list_stats(const int32_t* cell_rows, int64_t ncell, int64_t* status, long long* part,
-                             hipStream_t s)
-{
-    const int nb = (int)(ceil_div(ncell, kStreamBlock) < kStatsBlocks ? ceil_div(ncell, kStreamBlock)
-                                                                     : kStatsBlocks);
-    hipLaunchKernelGGL(k_rows_partial, dim3(nb), dim3(kStreamBlock), 0, s, cell_rows, ncell, part);
-    hipLaunchKernelGGL(k_rows_final, dim3(1), dim3(kStatsBlocks), 0, s, (const long long*)part, nb, status);
-    return hipGetLastError();
-}
-
-__global__ void k_gather_flags(const int64_t* __restrict__ status, const int64_t* __restrict__ err,
-                               const int64_t* __restrict__ flags, double* __restrict__ energy,
-                               const int64_t* __restrict__ tmax, unsigned long long* __restrict__ mx,
-                               int64_t* __restrict__ out, FlagGate g)
+// The flags of the state read back in one copy, by one wave (FlagGate in
+// md_internal.h).
+__device__ __forceinline__ void gather_flags(const int64_t status[4], const GatherIo& io, const FlagGate& g)
 {
     // wave-wide maxima over the slots: largest staged tile neighbourhood,
     // largest squared displacement and drift speed (bit patterns of
     // non-negative doubles order like the values)
+    const int lane = (int)lane_id();
     const bool step = g.run.gate != nullptr, folded = g.run.slots != nullptr;
     const int32_t stopped = step && (folded || g.run.idx > 1) ? g.run.gate[0] : 0;
     // a run already stopped: leave out (and the slots) as the stopping gather left them
@@ -358,21 +280,21 @@ __global__ void k_gather_flags(const int64_t* __restrict__ status, const int64_t
     const bool fold = !step || stopped || g.drift;
     int64_t m = 0;
     unsigned long long md = 0, mv = 0;
-    for (int k = threadIdx.x; k < kTileMaxSlots; k += 64) m = max(m, tmax[k]);
+    for (int k = lane; k < kTileMaxSlots; k += 64) m = max(m, io.tmax[k]);
     if (folded) {
         // the displacements of the last step that ran, set (ran - 1) % 3
-        if (threadIdx.x < kRunSlots) {
-            if (fold) md = run_set(g.run, ran + 2)[threadIdx.x * kMaxSlotStride];
+        if (lane < kRunSlots) {
+            if (fold) md = run_set(g.run, ran + 2)[lane * kMaxSlotStride];
             for (int k = 0; k < 3; ++k)
-                *(ulonglong2*)(run_set(g.run, k) + threadIdx.x * kMaxSlotStride) = make_ulonglong2(0ull, 0ull);
+                *(ulonglong2*)(run_set(g.run, k) + lane * kMaxSlotStride) = make_ulonglong2(0ull, 0ull);
         }
     } else if (fold) {
-        for (int k = threadIdx.x; k < kMaxSlots; k += 64) {
-            md = max(md, mx[k * kMaxSlotStride]);
-            mv = max(mv, mx[(kMaxSlots + k) * kMaxSlotStride]);
+        for (int k = lane; k < kMaxSlots; k += 64) {
+            md = max(md, io.mx[k * kMaxSlotStride]);
+            mv = max(mv, io.mx[(kMaxSlots + k) * kMaxSlotStride]);
             if (step) {
-                mx[k * kMaxSlotStride] = 0;
-                mx[(kMaxSlots + k) * kMaxSlotStride] = 0;
+                io.mx[k * kMaxSlotStride] = 0;
+                io.mx[(kMaxSlots + k) * kMaxSlotStride] = 0;
             }
         }
     }
@@ -382,34 +304,127 @@ __global__ void k_gather_flags(const int64_t* __restrict__ status, const int64_t
         md = max(md, (unsigned long long)__shfl_xor((long long)md, o, 64));
         mv = max(mv, (unsigned long long)__shfl_xor((long long)mv, o, 64));
     }
-    if (threadIdx.x != 0) return;
+    if (lane != 0) return;
     if (fold) {
-        energy[4] = __longlong_as_double((long long)md);
-        energy[5] = __longlong_as_double((long long)mv);
+        io.energy[4] = __longlong_as_double((long long)md);
+        io.energy[5] = __longlong_as_double((long long)mv);
     }
+    int64_t* __restrict__ out = io.out;
     out[0] = status[0];
     out[1] = status[1];
     out[2] = status[2];
     out[3] = status[3];
-    out[4] = err[0];
-    out[5] = err[1];
-    out[6] = flags[0];
-    out[7] = __double_as_longlong(energy[4]);
-    out[8] = __double_as_longlong(energy[5]);
-    out[9] = err[4];    // large-displacement check: member count
-    out[10] = err[5];   // large-displacement check: violation flag
+    out[4] = io.err[0];
+    out[5] = io.err[1];
+    out[6] = io.flags[0];
+    out[7] = __double_as_longlong(io.energy[4]);
+    out[8] = __double_as_longlong(io.energy[5]);
+    out[9] = io.err[4];    // large-displacement check: member count
+    out[10] = io.err[5];   // large-displacement check: violation flag
     out[11] = m;        // tiled list: largest staged neighbourhood of a tile
-    const int32_t stop = step && ((flags[0] & 1) != 0 || (fold && energy[4] > g.run.thr2)) ? 1 : 0;
+    const int32_t stop = step && ((io.flags[0] & 1) != 0 || (fold && io.energy[4] > g.run.thr2)) ? 1 : 0;
     out[12] = ran;
     out[13] = stop;
     if (step) g.run.gate[0] = folded ? 0 : stop;
 }
 
-hipError_t launch_gather_flags(const int64_t* status, const int64_t* err, const int64_t* flags, double* energy,
-                               const int64_t* tmax, unsigned long long* mx, int64_t* out, hipStream_t s,
-                               const FlagGate& gate)
+__global__ __launch_bounds__(64) void k_gather_flags(const int64_t* __restrict__ status, GatherIo io, FlagGate g)
 {
-    hipLaunchKernelGGL(k_gather_flags, dim3(1), dim3(64), 0, s, status, err, flags, energy, tmax, mx, out, gate);
+    const int64_t st[4] = {status[0], status[1], status[2], status[3]};
+    gather_flags(st, io, g);
+}
+
+hipError_t launch_gather_flags(const int64_t* status, const GatherIo& io, hipStream_t s, const FlagGate& gate)
+{
+    hipLaunchKernelGGL(k_gather_flags, dim3(1), dim3(64), 0, s, status, io, gate);
+    return hipGetLastError();
+}
+
+// List statistics: per-block (sum, stride needed) partials, then one block
+// combines them in order (and gathers the flags that the host reads next); small
+// grids in the last block alone.
+constexpr int kStatsBlocks = 1024;
+constexpr int64_t kStatsOneCells = 8192;
+
+__device__ __forceinline__ void stats_of(const ListStats& l, int64_t i0, int64_t stride, long long& sum, long long& mx)
+{
+#pragma unroll 4
+    for (int64_t c = i0; c < l.ncell; c += stride) {
+        const long long r = l.cell_rows[c];
+        sum += r;
+        if (l.ntile == 0) mx = r > mx ? r : mx;
+    }
+    for (int64_t t = i0; t < l.ntile; t += stride) {
+        const int cells = (int)t % l.nt == l.nt - 1 ? l.last_cells : l.tc;
+        const long long r = (l.tile_used[t] + cells - 1) / cells;
+        mx = r > mx ? r : mx;
+    }
+}
+
+// (sum, max) of the block in thread 0 .. 63 of it
+template <int BLOCK>
+__device__ __forceinline__ void block_stats(long long& sum, long long& mx)
+{
+    __shared__ long long s_sum[BLOCK / 64], s_max[BLOCK / 64];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        sum += __shfl_xor(sum, o, 64);
+        const long long y = __shfl_xor(mx, o, 64);
+        mx = y > mx ? y : mx;
+    }
+    if ((threadIdx.x & 63) == 0) {
+        s_sum[threadIdx.x >> 6] = sum;
+        s_max[threadIdx.x >> 6] = mx;
+    }
+    __syncthreads();
+    sum = mx = 0;
+    for (int w = 0; w < BLOCK / 64; ++w) {
+        sum += s_sum[w];
+        mx = s_max[w] > mx ? s_max[w] : mx;
+    }
+}
+
+__global__ __launch_bounds__(kStreamBlock) void k_stats_partial(ListStats l)
+{
+    long long sum = 0, mx = 0;
+    stats_of(l, (int64_t)blockIdx.x * kStreamBlock + threadIdx.x, (int64_t)gridDim.x * kStreamBlock, sum, mx);
+    block_stats<kStreamBlock>(sum, mx);
+    if (threadIdx.x == 0) {
+        l.part[2 * blockIdx.x] = sum;
+        l.part[2 * blockIdx.x + 1] = mx;
+    }
+}
+
+__global__ __launch_bounds__(kStatsBlocks) void k_stats_final(ListStats l, int nb, int gather, GatherIo io)
+{
+    long long sum = 0, mx = 0;
+    if (nb == 0) {
+        stats_of(l, threadIdx.x, kStatsBlocks, sum, mx);
+    } else if ((int)threadIdx.x < nb) {
+        sum = l.part[2 * threadIdx.x];
+        mx = l.part[2 * threadIdx.x + 1];
+    }
+    block_stats<kStatsBlocks>(sum, mx);
+    if (threadIdx.x >= 64) return;
+    if (threadIdx.x == 0) {
+        l.status[0] = sum;
+        l.status[1] = mx;
+    }
+    if (gather) {
+        const int64_t st[4] = {sum, mx, l.status[2], l.status[3]};
+        gather_flags(st, io, FlagGate());
+    }
+}
+
+hipError_t launch_list_stats(const ListStats& l, const GatherIo* gather, hipStream_t s)
+{
+    int nb = 0;
+    if (l.ncell > kStatsOneCells) {
+        nb = (int)std::min<int64_t>(ceil_div(l.ncell, kStreamBlock), kStatsBlocks);
+        hipLaunchKernelGGL(k_stats_partial, dim3(nb), dim3(kStreamBlock), 0, s, l);
+    }
+    hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(kStatsBlocks), 0, s, l, nb, gather ? 1 : 0,
+                       gather ? *gather : GatherIo());
     return hipGetLastError();
 }
 

@@ -359,6 +359,23 @@ __device__ __forceinline__ void run_mark(const RunIo& r, const RunCheck& c, bool
 // ---------------------------------------------------------------------------
 // md_cells.hip
 hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t count, hipStream_t s);
+// int32 arrays cleared together in one launch
+struct ClearList {
+    static constexpr int kMost = 4;
+    int32_t* p[kMost] = {};
+    int64_t words[kMost] = {};
+    void add(void* q, int64_t n)
+    {
+        int k = 0;
+        while (words[k] != 0) ++k;
+        p[k] = (int32_t*)q;
+        words[k] = n;
+    }
+};
+hipError_t launch_clear(const ClearList& l, hipStream_t s);
+// cells.count must be clear before launch_bin (it is written whole where
+// bin_clears_counts is false)
+bool bin_clears_counts(const Geo& g);
 hipError_t launch_bin(const Geo& g, const double* pos, const md_cells& cells, void* ws,
                       const WsLayout& L, int64_t* err_flags, hipStream_t s);
 hipError_t launch_resort(const Geo& g, const int32_t* order, const double* pos, const double* vel,
@@ -379,9 +396,22 @@ hipError_t launch_ref_copy(const Geo& g, const double* pos, const int32_t* cell_
 // tile_max[0 .. kTileMaxSlots) (atomic max into slot tile % kTileMaxSlots, so
 // that the atomics do not all meet at one address).  waves: MD_BUILD_* (tiled
 // builds only).
+// list.status[2], tile_max and, tiled, the tile counters (ws, L.tile_used)
+// must be clear (build_clears).  The list's statistics go to list.status at the
+// end, and with them, given gather, the flags as by launch_gather_flags.
+struct GatherIo {
+    const int64_t* err;
+    const int64_t* flags;
+    double* energy;
+    const int64_t* tmax;
+    unsigned long long* mx;
+    int64_t* out;
+};
+void build_clears(const Geo& g, const md_pairlist& list, void* ws, const WsLayout& L, bool tiled,
+                  unsigned long long* tile_max, ClearList& c);
 hipError_t launch_build(const Geo& g, double rs, const double* pos, const md_cells& cells,
                         const md_pairlist& list, void* ws, const WsLayout& L, bool tiled, bool half,
-                        unsigned long long* tile_max, int waves, hipStream_t s);
+                        unsigned long long* tile_max, int waves, const GatherIo* gather, hipStream_t s);
 
 // md_forces.hip
 struct ForceOut {
@@ -469,11 +499,21 @@ struct FlagGate {
     bool drift = false;
 };
 // Also folds the slot maxima of d2 and v2 (mx) into energy[4] and energy[5].
-hipError_t launch_gather_flags(const int64_t* status, const int64_t* err, const int64_t* flags, double* energy,
-                               const int64_t* tmax, unsigned long long* mx, int64_t* out, hipStream_t s,
+hipError_t launch_gather_flags(const int64_t* status, const GatherIo& io, hipStream_t s,
                                const FlagGate& gate = FlagGate());
-hipError_t launch_list_stats(const int32_t* cell_rows, int64_t ncell, int64_t* status, long long* part,
-                             hipStream_t s);
+// Statistics of a list into status: [0] total entries, [1] the stride needed: the
+// largest cell block or, tiled (ntile > 0), the largest ceil(entries / cells) of
+// the tiles, nt per column of tc cells and a last one of last_cells.
+struct ListStats {
+    const int32_t* cell_rows;
+    int64_t ncell;
+    const int32_t* tile_used;
+    int64_t ntile;
+    int32_t nt, tc, last_cells;
+    int64_t* status;
+    long long* part;          // long long[2 * 1024]
+};
+hipError_t launch_list_stats(const ListStats& l, const GatherIo* gather, hipStream_t s);
 
 // md_validity.hip
 hipError_t launch_ldc_disp(const Geo& g, const double* pos, const double* pos_ref, unsigned long long* max_d2,

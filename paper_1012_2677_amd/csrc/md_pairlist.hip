@@ -687,39 +687,6 @@ __global__ __launch_bounds__(64 * W) void k_build(BuildArgs a)
     }
 }
 
-// Stride a tiled list needs: the largest ceil(tile total / cells of the tile)
-// over the tiles (block maxima, then one block), into status[1].  Tile totals
-// and counts stay below 2^31.
-constexpr int kNeedBlocks = 1024;
-__device__ __forceinline__ int block_max_256(int m)
-{
-    __shared__ int s_m[4];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
-    if ((threadIdx.x & 63) == 0) s_m[threadIdx.x >> 6] = m;
-    __syncthreads();
-    return max(max(s_m[0], s_m[1]), max(s_m[2], s_m[3]));
-}
-__global__ __launch_bounds__(256) void k_tile_need(const int32_t* __restrict__ tile_used, int32_t ntile, int32_t nt,
-                                                   int32_t tc, int32_t last_cells, int32_t* __restrict__ part)
-{
-    int m = 0;
-    for (int t = blockIdx.x * 256 + threadIdx.x; t < ntile; t += gridDim.x * 256) {
-        const int cells = (t % nt) == nt - 1 ? last_cells : tc;
-        m = max(m, (tile_used[t] + cells - 1) / cells);
-    }
-    m = block_max_256(m);
-    if (threadIdx.x == 0) part[blockIdx.x] = m;
-}
-__global__ __launch_bounds__(256) void k_tile_need_final(const int32_t* __restrict__ part, int nb,
-                                                         int64_t* __restrict__ status)
-{
-    int m = 0;
-    for (int b = threadIdx.x; b < nb; b += 256) m = max(m, part[b]);
-    m = block_max_256(m);
-    if (threadIdx.x == 0) status[1] = m;
-}
-
 // Four waves per cell up to this many cells.  Time of a rebuild's list (build
 // and statistics, us, one / four waves per cell): 343 cells at 12 particles
 // each 31.0 / 25.5, 343 at 32 each 49.8 / 32.4, 64 at 32 each 69.7 / 37.8;
@@ -729,9 +696,19 @@ __global__ __launch_bounds__(256) void k_tile_need_final(const int32_t* __restri
 constexpr int64_t kWideCells = 1024;
 
 
+void build_clears(const Geo& g, const md_pairlist& list, void* ws, const WsLayout& L, bool tiled,
+                  unsigned long long* tile_max, ClearList& c)
+{
+    c.add(list.status, 8);
+    if (tiled) {
+        c.add(tile_max, 2 * kTileMaxSlots);
+        c.add((char*)ws + L.tile_used, g.ntile);
+    }
+}
+
 hipError_t launch_build(const Geo& g, double rs, const double* pos, const md_cells& cells,
                         const md_pairlist& list, void* ws, const WsLayout& L, bool tiled, bool half,
-                        unsigned long long* tile_max, int waves, hipStream_t s)
+                        unsigned long long* tile_max, int waves, const GatherIo* gather, hipStream_t s)
 {
     int32_t* tile_used = (int32_t*)((char*)ws + L.tile_used);
     BuildArgs a;
@@ -781,11 +758,6 @@ hipError_t launch_build(const Geo& g, double rs, const double* pos, const md_cel
     // smaller register sets
     const bool seq = tiled && (waves == MD_BUILD_TILE_WAVES ||
                                (waves == MD_BUILD_AUTO && g.ntile >= MD_BUILD_TILE_MIN && nch <= 8));
-    // status[2] (overflow) is cleared by the statistics kernel of the previous
-    // build or by the caller; clear it here on the stream before the build.
-    hipError_t e = launch_fill_i32((int32_t*)list.status, 0, 8, s);
-    if (e != hipSuccess) return e;
-    if (tiled && !seq && (e = launch_fill_i32(tile_used, 0, g.ntile, s)) != hipSuccess) return e;
     const dim3 grid((unsigned)(seq ? g.ntile : g.ncell));
     const bool wide = !seq && !half && g.ncell <= kWideCells;
 #define MD_BUILD_LAUNCH(N, TILED, HALF, SEQ, W) \
@@ -814,18 +786,18 @@ hipError_t launch_build(const Geo& g, double rs, const double* pos, const md_cel
         else MD_BUILD_LAUNCH(20, false, false, false, 1);
     }
 #undef MD_BUILD_LAUNCH
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    e = launch_list_stats(a.cell_rows, g.ncell, list.status, (long long*)((char*)ws + L.red), s);
-    if (e != hipSuccess || !tiled) return e;
-    // the statistics are read: their scratch takes the tiles' block maxima
-    int32_t* part = (int32_t*)((char*)ws + L.red);
-    const int nb = (int)std::min<int64_t>(ceil_div(g.ntile, 256), kNeedBlocks);
-    const int last_cells = g.nc[2] - (g.nt - 1) * g.tc;
-    hipLaunchKernelGGL(k_tile_need, dim3(nb), dim3(256), 0, s, tile_used, (int32_t)g.ntile, g.nt, g.tc, last_cells,
-                       part);
-    hipLaunchKernelGGL(k_tile_need_final, dim3(1), dim3(256), 0, s, (const int32_t*)part, nb, list.status);
-    return hipGetLastError();
+    if (hipError_t e = hipGetLastError()) return e;
+    ListStats st;
+    st.cell_rows = a.cell_rows;
+    st.ncell = g.ncell;
+    st.tile_used = tile_used;
+    st.ntile = tiled ? g.ntile : 0;
+    st.nt = g.nt;
+    st.tc = g.tc;
+    st.last_cells = g.nc[2] - (g.nt - 1) * g.tc;
+    st.status = list.status;
+    st.part = (long long*)((char*)ws + L.red);
+    return launch_list_stats(st, gather, s);
 }
 
 }  // namespace md
