@@ -264,10 +264,28 @@ hipError_t launch_reduce_pair(const double* part, int64_t nb, double scale0, dou
     return hipGetLastError();
 }
 
-// The flags of the state read back in one copy, by one wave (FlagGate in
+// The flags also to host memory that the device can write, given one: all words
+// with the call's number and their exclusive or, in one store of 16 lanes; the
+// host polls for a set of words that belong together.
+__device__ __forceinline__ void publish_flags(const int64_t* s_out, const GatherIo& io)
+{
+    if (!io.host) return;
+    const int lane = (int)lane_id();
+    __builtin_amdgcn_wave_barrier();
+    int64_t v = lane < kFlagWords ? s_out[lane] : 0;
+    int64_t x = v;
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) x ^= (int64_t)__shfl_xor((long long)x, o, 64);
+    if (lane == kFlagWords) v = io.seq;
+    if (lane == kFlagWords + 1) v = x ^ io.seq;
+    if (lane < kFlagWords + 2) io.host[lane] = v;
+}
+
+// The flags of the state that the host reads, by one wave (FlagGate in
 // md_internal.h).
 __device__ __forceinline__ void gather_flags(const int64_t status[4], const GatherIo& io, const FlagGate& g)
 {
+    __shared__ int64_t s_out[kFlagWords];
     // wave-wide maxima over the slots: largest staged tile neighbourhood,
     // largest squared displacement and drift speed (bit patterns of
     // non-negative doubles order like the values)
@@ -275,7 +293,11 @@ __device__ __forceinline__ void gather_flags(const int64_t status[4], const Gath
     const bool step = g.run.gate != nullptr, folded = g.run.slots != nullptr;
     const int32_t stopped = step && (folded || g.run.idx > 1) ? g.run.gate[0] : 0;
     // a run already stopped: leave out (and the slots) as the stopping gather left them
-    if (stopped && !folded) return;
+    if (stopped && !folded) {
+        if (lane < kFlagWords) s_out[lane] = io.out[lane];
+        publish_flags(s_out, io);
+        return;
+    }
     const int32_t ran = stopped ? g.run.gate[1] : g.run.idx;
     const bool fold = !step || stopped || g.drift;
     int64_t m = 0;
@@ -304,28 +326,30 @@ __device__ __forceinline__ void gather_flags(const int64_t status[4], const Gath
         md = max(md, (unsigned long long)__shfl_xor((long long)md, o, 64));
         mv = max(mv, (unsigned long long)__shfl_xor((long long)mv, o, 64));
     }
-    if (lane != 0) return;
-    if (fold) {
-        io.energy[4] = __longlong_as_double((long long)md);
-        io.energy[5] = __longlong_as_double((long long)mv);
+    if (lane == 0) {
+        if (fold) {
+            io.energy[4] = __longlong_as_double((long long)md);
+            io.energy[5] = __longlong_as_double((long long)mv);
+        }
+        const double d2 = fold ? __longlong_as_double((long long)md) : io.energy[4];
+        const double v2 = fold ? __longlong_as_double((long long)mv) : io.energy[5];
+        const int32_t stop = step && ((io.flags[0] & 1) != 0 || (fold && d2 > g.run.thr2)) ? 1 : 0;
+        for (int k = 0; k < 4; ++k) s_out[k] = status[k];
+        s_out[4] = io.err[0];
+        s_out[5] = io.err[1];
+        s_out[6] = io.flags[0];
+        s_out[7] = __double_as_longlong(d2);
+        s_out[8] = __double_as_longlong(v2);
+        s_out[9] = io.err[4];     // large-displacement check: member count
+        s_out[10] = io.err[5];    // large-displacement check: violation flag
+        s_out[11] = m;            // tiled list: largest staged neighbourhood of a tile
+        s_out[12] = ran;
+        s_out[13] = stop;
+        if (step) g.run.gate[0] = folded ? 0 : stop;
     }
-    int64_t* __restrict__ out = io.out;
-    out[0] = status[0];
-    out[1] = status[1];
-    out[2] = status[2];
-    out[3] = status[3];
-    out[4] = io.err[0];
-    out[5] = io.err[1];
-    out[6] = io.flags[0];
-    out[7] = __double_as_longlong(io.energy[4]);
-    out[8] = __double_as_longlong(io.energy[5]);
-    out[9] = io.err[4];    // large-displacement check: member count
-    out[10] = io.err[5];   // large-displacement check: violation flag
-    out[11] = m;        // tiled list: largest staged neighbourhood of a tile
-    const int32_t stop = step && ((io.flags[0] & 1) != 0 || (fold && io.energy[4] > g.run.thr2)) ? 1 : 0;
-    out[12] = ran;
-    out[13] = stop;
-    if (step) g.run.gate[0] = folded ? 0 : stop;
+    __builtin_amdgcn_wave_barrier();
+    if (lane < kFlagWords) io.out[lane] = s_out[lane];
+    publish_flags(s_out, io);
 }
 
 __global__ __launch_bounds__(64) void k_gather_flags(const int64_t* __restrict__ status, GatherIo io, FlagGate g)

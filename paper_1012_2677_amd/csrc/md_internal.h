@@ -399,13 +399,16 @@ hipError_t launch_ref_copy(const Geo& g, const double* pos, const int32_t* cell_
 // list.status[2], tile_max and, tiled, the tile counters (ws, L.tile_used)
 // must be clear (build_clears).  The list's statistics go to list.status at the
 // end, and with them, given gather, the flags as by launch_gather_flags.
+constexpr int kFlagWords = 14;
 struct GatherIo {
     const int64_t* err;
     const int64_t* flags;
     double* energy;
     const int64_t* tmax;
     unsigned long long* mx;
-    int64_t* out;
+    int64_t* out;                 // kFlagWords words on the device
+    int64_t* host = nullptr;      // and kFlagWords + 2 on the host, or nullptr
+    int64_t seq = 0;              // marks them
 };
 void build_clears(const Geo& g, const md_pairlist& list, void* ws, const WsLayout& L, bool tiled,
                   unsigned long long* tile_max, ClearList& c);

@@ -5,6 +5,9 @@ look at a gate that a pass of its own sets.  The same box as 21,952 one-cell
 tiles (gate) and as the automatic tiles (folded) must take the same steps
 bitwise, rebuild at the same ones, and equal a wait after every step; slot lists
 on either side of the limit against a wait after every step.
+
+The host reads a run's flags from pinned memory that the device writes, or, given
+ordinary memory or none, by a copy: the same steps either way.
 """
 
 import pytest
@@ -46,3 +49,22 @@ def test_slot_lists_on_either_side_of_the_fold(n_fcc):
     b = _run(q, v, L, 14, precision="fp64", resort_every=0, step_run=1)
     assert a.rebuilds == b.rebuilds > 1
     assert torch.equal(a.pos, b.pos) and torch.equal(a.vel, b.vel)
+
+
+@pytest.mark.parametrize("rule", ["half_skin", "dutc_ldc"])
+def test_flags_through_pinned_ordinary_and_no_memory(rule):
+    from paper_1012_2677_amd import Engine
+
+    q, L = li.jittered_fcc(10, amp=0.08, seed=5)
+    v = li.maxwell_boltzmann(len(q), T=1.5, seed=5)
+    runs = []
+    for memory in ("pinned", "ordinary", "none"):
+        e = Engine(q, v, L, precision="fp64", rebuild_rule=rule, device="cuda:0")
+        if memory != "pinned":
+            e.host_scratch = torch.zeros(16, dtype=torch.int64) if memory == "ordinary" else None
+            e.state.host_scratch = e.host_scratch.data_ptr() if memory == "ordinary" else None
+        log = e.step(60, sample_every=10)
+        runs.append((e, log))
+    for e, log in runs[1:]:
+        assert e.rebuilds == runs[0][0].rebuilds > 3
+        assert (log == runs[0][1]).all() and torch.equal(e.pos, runs[0][0].pos)
