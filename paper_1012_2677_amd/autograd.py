@@ -215,8 +215,7 @@ class TrajectoryMeanPE(torch.autograd.Function):
         ckpts = []
         total = 0.0
         k = 0
-        eng = Engine(q.cpu().numpy(), v.cpu().numpy(), box, eps=e_, sigma=s_, rc=rc, rs=rs, dt=dt,
-                     precision="fp64", resort_every=0, device=dev)
+        eng = Engine._on_device(q, v, box, eps=e_, sigma=s_, rc=rc, rs=rs, dt=dt, precision="fp64", resort_every=0)
         while k < steps:
             ckpts.append((eng.pos[:, :3].clone(), eng.vel.t().clone()))
             m = min(ckpt, steps - k)
@@ -251,8 +250,8 @@ class TrajectoryMeanPE(torch.autograd.Function):
         # builds its lists at those states only
         k_end = K
         # one engine recomputes every segment, reset from each checkpoint
-        eng = Engine(np.zeros((n, 3)), np.zeros((n, 3)), cfg["box"], eps=cfg["eps"], sigma=cfg["sigma"],
-                     rc=cfg["rc"], rs=cfg["rs"], dt=dt, precision="fp64", resort_every=0, device=dev)
+        eng = Engine._on_device(*ctx.ckpts[0], cfg["box"], eps=cfg["eps"], sigma=cfg["sigma"], rc=cfg["rc"],
+                                rs=cfg["rs"], dt=dt, precision="fp64", resort_every=0)
         # the field's list builds do not wait for their overflow flags: the
         # flags are read once per segment, and a segment whose list overflowed
         # is swept again from its saved adjoints with a grown list

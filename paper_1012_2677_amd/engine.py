@@ -180,7 +180,33 @@ class Engine:
                  step_run=0, build_waves="auto", device="cuda", cell_stride=None, timers=False):
         pos = np.ascontiguousarray(np.asarray(pos, dtype=np.float64))
         vel = np.ascontiguousarray(np.asarray(vel, dtype=np.float64))
-        n = pos.shape[0]
+        p4 = np.zeros((pos.shape[0], 4))
+        p4[:, :3] = pos
+        self._setup(p4.shape[0], box, lambda dev: (torch.from_numpy(p4).to(dev),
+                                                   torch.from_numpy(np.ascontiguousarray(vel.T)).to(dev)),
+                    eps=eps, sigma=sigma, rc=rc, rs=rs, dt=dt, precision=precision, resort_every=resort_every,
+                    rebuild_rule=rebuild_rule, ldc_max=ldc_max, list_layout=list_layout, tile_cells=tile_cells,
+                    step_run=step_run, build_waves=build_waves, device=device, cell_stride=cell_stride, timers=timers)
+
+    @classmethod
+    def _on_device(cls, pos: torch.Tensor, vel: torch.Tensor, box, **kw):
+        """An engine whose state starts as copies of device tensors (N, 3)
+        float64, made on the device."""
+        def arrays(dev):
+            p4 = torch.zeros((pos.shape[0], 4), dtype=torch.float64, device=dev)
+            p4[:, :3].copy_(pos)
+            v3 = torch.empty((3, vel.shape[0]), dtype=torch.float64, device=dev)
+            return p4, v3.copy_(vel.t())
+
+        e = cls.__new__(cls)
+        e._setup(int(pos.shape[0]), box, arrays, device=pos.device, **kw)
+        return e
+
+    def _setup(self, n, box, arrays, *, eps=1.0, sigma=1.0, rc=2.5, rs=2.8, dt=0.005, precision="fp64",
+               resort_every=1, rebuild_rule="half_skin", ldc_max=8192, list_layout="auto", tile_cells=0,
+               step_run=0, build_waves="auto", device="cuda", cell_stride=None, timers=False):
+        """Buffers and state; arrays(device) gives pos [N, 4] and vel [3, N]
+        there, which the engine keeps."""
         self.device = torch.device(device)
         if self.device.index is None:
             self.device = torch.device("cuda", torch.cuda.current_device())
@@ -199,10 +225,7 @@ class Engine:
         tiled = self.params.list_layout == A.MD_LIST_AUTO and resort_every > 0
         self.plist = PairList(self.params, self.grid.ncell, dev, cell_stride, entry_bits=16 if tiled else 32)
         self.ws = Workspace(self.params, dev)
-        p4 = np.zeros((n, 4))
-        p4[:, :3] = pos
-        self.pos = torch.from_numpy(p4).to(dev)
-        self.vel = torch.from_numpy(np.ascontiguousarray(vel.T)).to(dev)
+        self.pos, self.vel = arrays(dev)
         self.id = torch.arange(n, dtype=torch.int32, device=dev)
         resort = resort_every > 0
         # second buffers: the re-sort writes all three; in FP64 every step also
