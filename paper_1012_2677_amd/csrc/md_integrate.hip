@@ -169,8 +169,11 @@ __device__ __forceinline__ double block_sum_1024(double v)
 
 // energy[0..3] = (KE, PE, W, KE + PE); also into log_row when given.  Two
 // fixed-order levels: block b sums its contiguous share of the partials into
-// part3[3b .. 3b+2], then one block sums those in block order.
+// part3[3b .. 3b+2], then one block sums those in block order.  Up to
+// kEnergyOne partials one block sums them itself (1000 partials: one launch of
+// 4.0 us instead of two of 4.4 and 4.3).
 constexpr int kEnergyBlocks = 256;
+constexpr int64_t kEnergyOne = 4096;
 __global__ __launch_bounds__(kReduceBlock) void k_reduce_energy_part(const double* __restrict__ part_pw, int64_t nbf,
                                                                      const double* __restrict__ part_ke, int64_t nbi,
                                                                      double* __restrict__ part3,
@@ -197,13 +200,21 @@ __global__ __launch_bounds__(kReduceBlock) void k_reduce_energy_part(const doubl
 }
 
 __global__ __launch_bounds__(kReduceBlock) void k_reduce_energy(const double* __restrict__ part3, int nb,
+                                                                const double* __restrict__ part_pw, int64_t nbf,
+                                                                const double* __restrict__ part_ke, int64_t nbi,
                                                                 double* __restrict__ energy,
                                                                 double* __restrict__ log_row,
                                                                 const int32_t* __restrict__ gate)
 {
     if (gate && gate[0]) return;
     double pe = 0.0, w = 0.0, ke = 0.0;
-    if ((int)threadIdx.x < nb) {
+    if (nb == 0) {
+        for (int64_t b = threadIdx.x; b < nbf; b += kReduceBlock) {
+            pe += part_pw[2 * b];
+            w += part_pw[2 * b + 1];
+        }
+        for (int64_t b = threadIdx.x; b < nbi; b += kReduceBlock) ke += part_ke[b];
+    } else if ((int)threadIdx.x < nb) {
         pe = part3[3 * threadIdx.x];
         w = part3[3 * threadIdx.x + 1];
         ke = part3[3 * threadIdx.x + 2];
@@ -230,11 +241,14 @@ hipError_t launch_reduce_energy(const double* part_pw, int64_t nbf, const double
                                 const int32_t* gate)
 {
     const int64_t most = nbf > nbi ? nbf : nbi;
-    const int nb = (int)std::min<int64_t>(std::max<int64_t>(ceil_div(most, kReduceBlock), 1), kEnergyBlocks);
-    hipLaunchKernelGGL(k_reduce_energy_part, dim3(nb), dim3(kReduceBlock), 0, s, part_pw, nbf, part_ke, nbi,
-                       scratch, gate);
-    hipLaunchKernelGGL(k_reduce_energy, dim3(1), dim3(kReduceBlock), 0, s, (const double*)scratch, nb, energy,
-                       log_row, gate);
+    int nb = 0;
+    if (most > kEnergyOne) {
+        nb = (int)std::min<int64_t>(ceil_div(most, kReduceBlock), kEnergyBlocks);
+        hipLaunchKernelGGL(k_reduce_energy_part, dim3(nb), dim3(kReduceBlock), 0, s, part_pw, nbf, part_ke, nbi,
+                           scratch, gate);
+    }
+    hipLaunchKernelGGL(k_reduce_energy, dim3(1), dim3(kReduceBlock), 0, s, (const double*)scratch, nb, part_pw, nbf,
+                       part_ke, nbi, energy, log_row, gate);
     return hipGetLastError();
 }
 
