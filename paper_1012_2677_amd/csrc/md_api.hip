@@ -1090,9 +1090,12 @@ static int step_runs(const Ctx& c, const md_params* p, md_state* st, int64_t nst
             rio.gate = gate;
             rio.idx = (int32_t)b;
             rio.thr2 = thr2;
-            if (traj)
+            const bool records = traj && step_records(p->precision, st->list, tile_io(st));
+            if (traj && !records)
                 MD_HIP(launch_record(c.g, P, st->id, traj + 4 * c.g.n * (done + b), s, rio), "step/record");
             StepIo io;
+            io.id = st->id;
+            io.frame = records ? traj + 4 * c.g.n * (done + b) : nullptr;
             io.pos = P;
             io.pos32 = mixed ? P32 : nullptr;
             io.cell_xyz = st->cells.cell_xyz;

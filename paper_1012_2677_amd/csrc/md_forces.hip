@@ -77,6 +77,8 @@ struct PairArgs {
     int32_t max_slots;         // slots that the block maxima are spread over
     const int32_t* order;      // slot lists: slots in cell order (nullptr: they are in it)
     int32_t rounds;            // slot lists: rounds of 8 keys per wave
+    const int32_t* id;         // FP64 slot lists: particle of each slot and the frame that
+    double4* frame;            // takes the step's positions by particle (or nullptr)
 };
 
 // Keys [kb, ke) of logical block b of a half-list pass: a chunk of kForceBlock
@@ -350,6 +352,7 @@ __global__ __launch_bounds__(kForceBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_fp64(
     {
         const int64_t k = mykey;
         double4 p = a.pos[k];
+        if (MODE != MODE_FORCE && a.frame && myvalid) a.frame[a.id[k]] = make_double4(p.x, p.y, p.z, 0.0);
         p.w = (a.exact_all || boundary_cell(a.cell_xyz[k], a.nc)) ? 1.0 : 0.0;
         s_p[wave][lane] = p;
         s_off[wave][lane] = a.offsets[k];
@@ -1312,6 +1315,11 @@ hipError_t launch_forces(const Geo& g, const LJ& lj, int precision, const double
     return hipGetLastError();
 }
 
+bool step_records(int precision, const md_pairlist& list, const TileIo& tile)
+{
+    return precision == MD_FP64 && !list.half && tile.stage == 0;
+}
+
 hipError_t launch_force_step(const Geo& g, const LJ& lj, int precision, const StepIo& io, hipStream_t s)
 {
     if (hipError_t e = check_tiles(g, precision, io.tile)) return e;
@@ -1350,6 +1358,8 @@ hipError_t launch_force_step(const Geo& g, const LJ& lj, int precision, const St
         }
         return hipGetLastError();
     }
+    a.id = io.id;
+    a.frame = (double4*)io.frame;
     a.run = io.run;
     if (io.run.slots) {
         a.max_d2 = run_set(io.run, io.run.idx);

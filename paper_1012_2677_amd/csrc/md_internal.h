@@ -456,9 +456,15 @@ struct StepIo {
     double dt;
     bool drift;
     bool track_speed;             // also record the largest squared drift speed
+    const int32_t* id = nullptr;  // with frame
+    double* frame = nullptr;      // frame[id[slot]] = pos[slot] (step_records)
     TileIo tile;                  // tiled list (tile.stage > 0)
     RunIo run;                    // full list: the step's run of queued steps (run.gate: given from step 1 on by a gate)
 };
+// Whether launch_force_step itself records the positions it evaluates its forces
+// at (io.frame), which the FP64 slot-list pass has in its registers; otherwise
+// launch_record does, before it.
+bool step_records(int precision, const md_pairlist& list, const TileIo& tile);
 hipError_t launch_force_step(const Geo& g, const LJ& lj, int precision, const StepIo& io, hipStream_t s);
 int64_t pair_blocks(const Geo& g);   // blocks (and energy partials) of one pair-kernel launch
 int64_t force_blocks(const Geo& g, bool tiled, bool half);   // same for every list layout
