@@ -236,7 +236,6 @@ struct CellRows {
     int T, own_cnt;
     const double4* key;      // the cell's particles, w = slot
     E* rows;                 // this wave's row buffer
-    uint32_t* rowend;        // row ends, counted from the first row of their wave
     uint32_t* wused;         // W > 1: entries of each wave, then the cell's slice
     E* blk;                  // tiled: the tile's pool; slots: the cell's block
     uint64_t cap;            // entries of it
@@ -265,22 +264,22 @@ __device__ __forceinline__ uint32_t rows_from_registers(const BuildArgs& a, cons
     const int per = W > 1 ? (r.own_cnt + W - 1) / W : r.own_cnt;
     const int k0 = W > 1 ? min(r.wave * per, r.own_cnt) : 0, k1 = min(k0 + per, r.own_cnt);
     uint32_t used = 0;
+    uint32_t my_end = 0;     // lane j: end of the row of key k0 + j, counted from the first row of the wave
     int kk = k0;
     for (; kk < k1 && used + (uint32_t)r.T <= ROOM; ++kk) {
         used = row_staged<MINIMG, NACT, E, HALF>(a, lane, r.key[kk], kk, used, cx, cy, cz, meta, r.rows);
-        if (lane == 0) {
-            r.rowend[kk] = used;
-            if (TILED && (used & 1u)) r.rows[used] = (E)r.pad;
-        }
+        my_end = lane == kk - k0 ? used : my_end;
         used = row_start<E>(used);
     }
     const int ks = kk;
+    // the stand-ins that follow the staged rows of odd length
+    if (TILED && k0 + lane < ks && (my_end & 1u)) r.rows[my_end] = (E)r.pad;
     uint32_t staged = used;
     constexpr bool PACKED = !TILED && W == 1;
     for (; kk < k1; ++kk) {
         used = row_direct<MINIMG, NACT, E, HALF, PACKED>(a, lane, r.key[kk], kk, used, cx, cy, cz, meta, r.blk,
                                                          (uint32_t)r.cap, r.rows, ROOM);
-        if (lane == 0) r.rowend[kk] = used;
+        my_end = lane == kk - k0 ? used : my_end;
         used = row_start<E>(used);
     }
     uint32_t total = used, first = 0, base = 0;
@@ -330,9 +329,10 @@ __device__ __forceinline__ uint32_t rows_from_registers(const BuildArgs& a, cons
             w = row_start<E>(w);
         }
     }
+    const uint32_t prev = __shfl_up(my_end, 1, 64);
     if (k0 + lane < k1) {
         const int k2 = k0 + lane;
-        const uint32_t end = r.rowend[k2], beg = lane > 0 ? row_start<E>(r.rowend[k2 - 1]) : 0u;
+        const uint32_t end = my_end, beg = lane > 0 ? row_start<E>(prev) : 0u;
         const int32_t kslot = (int32_t)__double_as_longlong(r.key[k2].w);
         if constexpr (TILED) {
             // an overflowed cell (list invalid) keeps in-range, empty rows
@@ -477,7 +477,6 @@ __device__ __forceinline__ uint32_t build_cell(const BuildArgs& a, int cx, int c
     // margin); before that, the candidate table
     constexpr int kRows = rowbuf_words<NCH, W, E>();
     __shared__ __align__(8) uint32_t s_rows[W * kRows + 2];
-    __shared__ uint32_t s_rowend[kMaxOwn];
     __shared__ uint32_t s_wused[W + 1];
     __shared__ int s_lbase[27];
     const bool has_nb = lane < 27 && (!HALF || lane <= 13);
@@ -539,13 +538,14 @@ __device__ __forceinline__ uint32_t build_cell(const BuildArgs& a, int cx, int c
             meta[ch] = 0;
             if (ch * 64 >= T) continue;          // uniform: chunk beyond the neighbourhood
             const int tq = ch * 64 + lane;
-            const bool ok = tq < T;
-            const int te = ok ? tq : T - 1;   // in-range entry; discarded if tq >= T
+            const int te = min(tq, T - 1);   // in-range entry; discarded if tq >= T
             const uint32_t ex = s_tpos[te], ey = s_tcode[te];
-            const int32_t slot = a.order ? a.order[ex] : (int32_t)ex;
-            const double4 p = a.pos[slot];
+            const uint32_t slot = a.order ? (uint32_t)a.order[ex] : ex;
+            // (slots are below 2^27: a 32-bit byte offset from a uniform base)
+            const double4 p = *(const double4*)((const char*)a.pos + (slot << 5));
             // a NaN x alone fails the distance test in both forms of it
-            px[ch] = ok ? p.x : qnan;
+            px[ch] = p.x;
+            if ((ch + 1) * 64 > T) px[ch] = tq < T ? p.x : qnan;   // (uniform condition)
             py[ch] = p.y;
             pz[ch] = p.z;
             meta[ch] = TILED ? ey << 4 : ((uint32_t)slot | (ey << kCodeShift));
@@ -560,7 +560,6 @@ __device__ __forceinline__ uint32_t build_cell(const BuildArgs& a, int cx, int c
         r.own_cnt = own_cnt;
         r.key = s_key;
         r.rows = reinterpret_cast<E*>(s_rows + wave * kRows);
-        r.rowend = s_rowend;
         r.wused = s_wused;
         r.blk = TILED ? (E*)tx.tblk : blk;
         r.cap = TILED ? tx.tcap : (uint64_t)stride;
@@ -607,14 +606,27 @@ __device__ __forceinline__ uint32_t build_cell(const BuildArgs& a, int cx, int c
     return used;
 }
 
+// Waves per SIMD that the registers must leave room for.  Rebuild's list, us, at
+// this bound and at others: wave per tile, 6 chunks (142^3 cells) 7 waves 4880,
+// 6 5160, 8 5100, unbounded (92 registers, 5) 5480; wave per cell, 6 chunks
+// (71^3) 8 waves 644, 7 664; 8 chunks (28^3) 6 or 7 waves 75, 5 78, and with all
+// 8 chunks in use (1M at density 0.8) 298 and 278; 12 chunks (256k at 0.8) 5
+// waves 101, 4 105.
+template <int NCH, bool SEQ, int W>
+constexpr int build_waves_per_simd()
+{
+    if (NCH == 6) return SEQ ? 7 : 8;
+    return NCH == 8 ? 6 : (NCH == 12 && W == 1 ? 5 : 1);
+}
+
 // One wave per cell (four on small grids, whose cells alone would leave most of
-// the GPU idle while each wave walks its cell's keys), or (SEQ, tiled lists of large grids) one wave per tile
-// that builds the tile's cells one after another along z: the cells' slices
-// of the tile's pool then follow in cell order with no atomic, the tile's runs
-// and staged layout are worked out once, and the next cell's neighbour starts
-// and counts load while a cell is built.
+// the GPU idle while each wave walks its cell's keys), or (SEQ, tiled lists of
+// large grids) one wave per tile that builds the tile's cells one after another
+// along z: the cells' slices of the tile's pool then follow in cell order with
+// no atomic, the tile's runs and staged layout are worked out once, and the next
+// cell's neighbour starts and counts load while a cell is built.
 template <int NCH, bool TILED, bool HALF, bool SEQ, int W>
-__global__ __launch_bounds__(64 * W) void k_build(BuildArgs a)
+__global__ __launch_bounds__(64 * W, (build_waves_per_simd<NCH, SEQ, W>())) void k_build(BuildArgs a)
 {
     static_assert(!SEQ || (TILED && !HALF && W == 1), "tile-sequential builds write tiled full rows");
     const int64_t tb = xcd_remap(blockIdx.x, gridDim.x);
