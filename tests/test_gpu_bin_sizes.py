@@ -35,3 +35,22 @@ def test_bin_cells_at_the_edges(ref, n, L):
     assert np.array_equal(count, r_count)
     assert np.array_equal(start, r_start)
     assert np.array_equal(order, r_order)
+
+
+@pytest.mark.parametrize("d", [1, 23, 24, 25, 40, 64])
+def test_bin_cells_with_many_cells_in_a_wave(ref, d):
+    # 64 slots in a row fall into d cells, each cell coming up again and again:
+    # the lanes past the first 24 cells of a wave add to the counts alone
+    n, L, m = 20011, 57.5, 20
+    i = np.arange(n)
+    c = (i // 64 * 37 + i % 64 % d * 13) % m**3
+    corner = np.stack([c // (m * m), c // m % m, c % m], axis=1)
+    q = (corner + 0.05 + 0.9 * np.random.default_rng(d).random((n, 3))) * (L / m)
+    s = G.Standalone(q, L)
+    assert s.grid.ncell == (m, m, m)
+    cell_of, count, start, order, _ = s.bin()
+    r_cell, r_count, r_start, r_order = ref.bin_cells(q, L, s.grid.ncell)
+    assert np.array_equal(cell_of, r_cell)
+    assert np.array_equal(count, r_count)
+    assert np.array_equal(start, r_start)
+    assert np.array_equal(order, r_order)
