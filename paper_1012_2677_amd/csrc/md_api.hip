@@ -687,16 +687,21 @@ static int rebuild(const Ctx& c, const md_params* p, md_state* st, bool allow_re
     return MD_OK;
 }
 
-// Slot lists of a state that re-sorted a few rebuilds ago: its slots are still
-// close to the cell order, and the passes walk them as they lie, with coalesced
+// Slot lists of a state whose slots are close to the cell order, because it
+// re-sorted a few rebuilds ago: the passes walk them as they lie, with coalesced
 // keys.  Force pass, us, 2.1 million particles, slots as they lie / cell order, at
 // 20 rebuilds after the re-sort, 56, 93 and 149: FP64 383 / 389, 503 / 499, 579 /
-// 551, 665 / 600; mixed 242 / 270, 278 / 353, 313 / 397, 359 / 444.
+// 551, 665 / 600; mixed 242 / 270, 278 / 353, 313 / 397, 359 / 444.  A mixed state
+// that never re-sorts is walked as it lies, too, where its local coordinates
+// exceed an XCD's 4 MB of L2: its inputs usually come in some spatial order (20
+// steps of 1 million in lattice order 5.15 ms, in cell order 5.67; 25 of 95,000
+// 1.21 and 1.14; FP64, 20 of 500,000: 3.8 and 3.1).
 static bool near_cell_order(const md_params* p, const md_state* st)
 {
-    const int64_t most = p->precision == MD_MIXED ? 150 : 48;   // rebuilds
-    return p->resort_every > 0 && st->resorts > 0 && st->rebuilds > 0 &&
-           (st->rebuilds - 1) % p->resort_every < most;
+    const bool mixed = p->precision == MD_MIXED;
+    if (p->resort_every <= 0) return mixed && p->n > 262144;
+    const int64_t most = mixed ? 150 : 48;   // rebuilds
+    return st->resorts > 0 && st->rebuilds > 0 && (st->rebuilds - 1) % p->resort_every < most;
 }
 
 static TileIo tile_io(const md_params* p, const md_state* st)
