@@ -1044,7 +1044,6 @@ static int step_runs(const Ctx& c, const md_params* p, md_state* st, int64_t nst
         tick(T, MD_T_INTEGRATE, 1, s);
         st->phase = 1;
     }
-    MD_HIP(launch_fill_i32(gate, 0, 2, s), "step/gate");
     if ((rc = read_flags(c, st, F, s, f)) != MD_OK) return rc;
     timer_collect(T);
     double maxd2;

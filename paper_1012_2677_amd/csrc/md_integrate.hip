@@ -359,7 +359,7 @@ __device__ __forceinline__ void gather_flags(const int64_t status[4], const Gath
         s_out[11] = m;            // tiled list: largest staged neighbourhood of a tile
         s_out[12] = ran;
         s_out[13] = stop;
-        if (step) g.run.gate[0] = folded ? 0 : stop;
+        if (step) g.run.gate[0] = stop;
     }
     __builtin_amdgcn_wave_barrier();
     if (lane < kFlagWords) io.out[lane] = s_out[lane];

@@ -302,6 +302,10 @@ __device__ __forceinline__ double rcp64_1(double x)
 //     that set and decide for themselves, alike, and the first wave records a
 //     stop for the passes after them (gate[0] = 1, gate[1] = the steps that
 //     ran) or clears set (b + 2) % 3, last read by step b.
+// The gate of a run starts clear whatever the run before it left there: a
+// rebuild may change the list's layout, and with it the way of telling.  By a
+// gate, nothing reads it before the pass after step 0 has written it; folded,
+// the first wave of step 0, whose launch does not read it, clears it.
 // The fold saves a launch and its 3.4 to 6 us per step (4,000 particles FP64,
 // 100 steps: 3.11 to 2.63 ms per call, tiles as they are) and adds the wait
 // for 17 lines to the start of every block: 3 to 4% of a pass of many tiles
@@ -351,6 +355,7 @@ __device__ __forceinline__ void run_mark(const RunIo& r, const RunCheck& c, bool
         }
     } else if (lane_id() < kRunSlots) {
         *(ulonglong2*)(run_set(r, r.idx + 1) + lane_id() * kMaxSlotStride) = make_ulonglong2(0ull, 0ull);
+        if (r.idx == 0 && lane_id() < 2) r.gate[lane_id()] = 0;
     }
 }
 
@@ -501,7 +506,7 @@ hipError_t launch_reduce_pair(const double* part, int64_t nb, double scale0, dou
 // the next one must rebuild first or a force was not finite.  By a gate: after
 // every step idx, setting run.gate[0] when it stopped the run (the gathers after
 // it then leave out as the stopping one wrote it).  Folded (run.slots): once at
-// the run's end, idx the steps queued; clears the run's slots and gate.  drift:
+// the run's end, idx the steps queued; clears the run's slots.  drift:
 // step idx ends with a drift (all but the last of a call).
 struct FlagGate {
     RunIo run;                    // run.gate nullptr: a plain gather
