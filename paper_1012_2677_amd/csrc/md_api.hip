@@ -781,12 +781,12 @@ static bool flags_arrived(const md_state* st, const Flags& F, int64_t out[16])
 {
     const volatile int64_t* h = st->host_scratch;
     if (h[kFlagWords] != F.seq) return false;
-    int64_t x = F.seq;
+    uint64_t x = seal_mix((uint64_t)F.seq, kFlagWords);
     for (int k = 0; k < kFlagWords; ++k) {
         out[k] = h[k];
-        x ^= out[k];
+        x ^= seal_mix((uint64_t)out[k], k);
     }
-    return h[kFlagWords + 1] == x;
+    return (uint64_t)h[kFlagWords + 1] == x;
 }
 
 // Wait for the words of the last gather: list status [0..3], cell-grid

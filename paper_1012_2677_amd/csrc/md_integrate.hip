@@ -279,19 +279,18 @@ hipError_t launch_reduce_pair(const double* part, int64_t nb, double scale0, dou
 }
 
 // The flags also to host memory that the device can write, given one: all words
-// with the call's number and their exclusive or, in one store of 16 lanes; the
-// host polls for a set of words that belong together.
+// with the call's number and their seal, in one store of 16 lanes; the host
+// polls for a set of words that belong together.
 __device__ __forceinline__ void publish_flags(const int64_t* s_out, const GatherIo& io)
 {
     if (!io.host) return;
     const int lane = (int)lane_id();
     __builtin_amdgcn_wave_barrier();
-    int64_t v = lane < kFlagWords ? s_out[lane] : 0;
-    int64_t x = v;
+    int64_t v = lane < kFlagWords ? s_out[lane] : io.seq;
+    int64_t x = lane <= kFlagWords ? (int64_t)seal_mix((uint64_t)v, lane) : 0;
 #pragma unroll
     for (int o = 8; o > 0; o >>= 1) x ^= (int64_t)__shfl_xor((long long)x, o, 64);
-    if (lane == kFlagWords) v = io.seq;
-    if (lane == kFlagWords + 1) v = x ^ io.seq;
+    if (lane == kFlagWords + 1) v = x;
     if (lane < kFlagWords + 2) io.host[lane] = v;
 }
 

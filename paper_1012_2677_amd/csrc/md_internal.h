@@ -8,6 +8,7 @@
 #include <cstdint>
 
 #include "md.h"
+#include "md_seal.h"
 
 namespace md {
 
