@@ -241,8 +241,8 @@ __global__ __launch_bounds__(kStreamBlock) void k_scatter(int64_t n, const int32
 // waves in atomic order).  The cells of a block, CELLS of them, are
 // contiguous in `order`: when their slots fit, they are loaded into LDS, and
 // each slot's place in its cell is the number of smaller ones in it (a thread
-// per slot, ~11 reads each at rho = 0.5); otherwise a thread per cell sorts
-// its cell in place in global memory.  Few cells per block on small grids, which
+// per slot, ~11 reads each at rho = 0.5); otherwise the block takes its cells one
+// after another (sort_by_cell).  Few cells per block on small grids, which
 // otherwise have too few blocks (28^3 cells at 11.7 particles, 64, 32, 16, 8 per
 // block: 6.4, 5.1, 4.1, 5.7 us; an insertion sort by a thread per cell of 256
 // 17.5), more on large ones, where a block's three waits cost more (142^3 cells:
@@ -250,22 +250,63 @@ __global__ __launch_bounds__(kStreamBlock) void k_scatter(int64_t n, const int32
 constexpr int64_t kSortFewCells = 131072;
 constexpr int kSortLds = 4096;   // slots of one block's cells sorted in LDS
 
-__device__ __forceinline__ void insertion_sort(int32_t* v, int32_t len)
+// The same for the cells of a block that are too crowded together (a cutoff of
+// ten diameters puts a thousand particles in a cell), by the whole block: a cell
+// that fits is ordered in LDS, a larger one from a copy of it in tmp, which a block
+// reads through LDS in parts, each thread counting for kSortItems slots at a
+// time.  (20,000 particles in 27 cells: 1.6 ms a call of md_bin_cells; an
+// insertion sort in global memory by a thread per cell 40.)
+constexpr int kSortItems = 4;
+__device__ void sort_by_cell(int64_t c0, int nc, const int32_t* __restrict__ start, int32_t* __restrict__ order,
+                             int32_t* __restrict__ tmp, int32_t* s_o)
 {
-    for (int32_t k = 1; k < len; ++k) {
-        const int32_t x = v[k];
-        int32_t p = k - 1;
-        while (p >= 0 && v[p] > x) {
-            v[p + 1] = v[p];
-            --p;
+    const int tid = threadIdx.x;
+    for (int c = 0; c < nc; ++c) {
+        const int32_t b = start[c0 + c], len = start[c0 + c + 1] - b;
+        if (len < 2) continue;
+        __syncthreads();     // the cell before is read
+        if (len <= kSortLds) {
+            for (int t = tid; t < len; t += kStreamBlock) s_o[t] = order[b + t];
+            __syncthreads();
+            for (int t = tid; t < len; t += kStreamBlock) {
+                const int32_t x = s_o[t];
+                int r = 0;
+                for (int q = 0; q < len; ++q) r += s_o[q] < x;
+                order[b + r] = x;
+            }
+            continue;
         }
-        v[p + 1] = x;
+        for (int t = tid; t < len; t += kStreamBlock) tmp[b + t] = order[b + t];
+        __syncthreads();
+        for (int t0 = 0; t0 < len; t0 += kStreamBlock * kSortItems) {
+            int32_t x[kSortItems], r[kSortItems];
+#pragma unroll
+            for (int k = 0; k < kSortItems; ++k) {
+                const int t = t0 + k * kStreamBlock + tid;
+                x[k] = tmp[b + (t < len ? t : len - 1)];
+                r[k] = 0;
+            }
+            for (int p0 = 0; p0 < len; p0 += kSortLds) {
+                const int part = len - p0 < kSortLds ? len - p0 : kSortLds;
+                __syncthreads();
+                for (int t = tid; t < part; t += kStreamBlock) s_o[t] = tmp[b + p0 + t];
+                __syncthreads();
+                for (int q = 0; q < part; ++q) {
+                    const int32_t y = s_o[q];
+#pragma unroll
+                    for (int k = 0; k < kSortItems; ++k) r[k] += y < x[k];
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < kSortItems; ++k)
+                if (t0 + k * kStreamBlock + tid < len) order[b + r[k]] = x[k];
+        }
     }
 }
 
 template <int CELLS>
 __global__ __launch_bounds__(kStreamBlock) void k_sort_cells(int64_t ncell, const int32_t* __restrict__ start,
-                                                             int32_t* __restrict__ order)
+                                                             int32_t* __restrict__ order, int32_t* __restrict__ tmp)
 {
     __shared__ int32_t s_o[kSortLds];
     __shared__ uint8_t s_c[kSortLds];
@@ -277,7 +318,7 @@ __global__ __launch_bounds__(kStreamBlock) void k_sort_cells(int64_t ncell, cons
     __syncthreads();
     const int32_t b0 = s_start[0], len = s_start[nc] - b0;
     if (len > kSortLds) {
-        if (tid < nc) insertion_sort(order + s_start[tid], s_start[tid + 1] - s_start[tid]);
+        sort_by_cell(c0, nc, start, order, tmp, s_o);
         return;
     }
     for (int t = tid; t < len; t += kStreamBlock) s_o[t] = order[b0 + t];
@@ -438,7 +479,7 @@ hipError_t launch_bin(const Geo& g, const double* pos, const md_cells& cells, vo
     auto sort = [&](auto cells_per_block) {
         constexpr int CELLS = decltype(cells_per_block)::value;
         hipLaunchKernelGGL((k_sort_cells<CELLS>), dim3((unsigned)ceil_div(g.ncell, CELLS)), dim3(kStreamBlock), 0, s,
-                           g.ncell, (const int32_t*)cells.start, cells.order);
+                           g.ncell, (const int32_t*)cells.start, cells.order, rank);   // (ranks are read)
     };
     if (g.ncell <= kSortFewCells) sort(std::integral_constant<int, 16>());
     else sort(std::integral_constant<int, 128>());
