@@ -254,7 +254,12 @@ typedef struct md_timers {
  *   just past the tile's neighbourhood, counted in the list status but not
  *   in the row's count); tile_stage:
  *   the largest neighbourhood of a tile, in particles; tile_cells: the tile
- *   length along z in cells. */
+ *   length along z in cells.
+ *   slot_spread: the order of the slots at the last build without a re-sort (set
+ *   by the library): 1024 times the mean squared distance, in cells and at most
+ *   64 each, of slots that follow one another.  Slot lists are walked as the
+ *   slots lie while it is small and in cell order otherwise; the forces do not
+ *   depend on it, the last bits of the energy sums do. */
 typedef struct md_state {
     double*   pos;
     double*   vel;
@@ -285,7 +290,7 @@ typedef struct md_state {
     int32_t   list_tiled;
     int32_t   tile_stage;
     int32_t   tile_cells;
-    int32_t   reserved;
+    int32_t   slot_spread;
 } md_state;
 
 /* Host-only: cells per axis for these parameters.  MD_ERR_BOX when an axis

@@ -85,7 +85,7 @@ class MdState(C.Structure):
                 ("rebuilds", C.c_int64), ("resorts", C.c_int64), ("phase", C.c_int32),
                 ("list_valid", C.c_int32), ("dutc_buffer", C.c_double), ("ldc_checks", C.c_int64),
                 ("ldc_kept", C.c_int64), ("list_tiled", C.c_int32), ("tile_stage", C.c_int32),
-                ("tile_cells", C.c_int32), ("reserved", C.c_int32)]
+                ("tile_cells", C.c_int32), ("slot_spread", C.c_int32)]
 
 
 _lib = None

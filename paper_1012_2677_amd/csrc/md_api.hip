@@ -147,7 +147,8 @@ LJ make_lj(const md_params& p)
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Small device scalars in the workspace (int64 words):
-//   [0], [1]  cell-grid error flags         [2]  md_forces non-finite flag
+//   [0]       cell-grid error flags         [1]  order of a state's slots (launch_spread)
+//   [2]       md_forces non-finite flag     [3]  md_forces order of the slots
 //   [4]       large-displacement members    [5]  large-displacement violation
 //   [6]       largest squared displacement (md_ldc_check)
 //   [8]       gate of a run of queued steps (int32[2]; md_step)
@@ -405,22 +406,31 @@ int md_build_pairlist(const md_params* p, const double* pos, const md_cells* cel
 
 // The force pass of md_forces and md_forces_noalloc, with its scratch given:
 // pos32 (mixed precision: float4 per particle), part (2 doubles per block of
-// the pass) and one flag word (cleared here).
+// the pass), one flag word (cleared here) and the word after it.  Below
+// kSpreadMinN either walk takes the same time on ordered slots and the cell order
+// is right for the others; above it the pass learns the order of the slots first
+// (FP64, 4 million in lattice order: 588 us as the slots lie, 621 in cell order).
+constexpr int64_t kSpreadMinN = 524288;
 static int forces_with(const Ctx& c, const md_params* p, const double* pos, const md_cells* cells,
                        const md_pairlist* list, void* force, double* pe_w, float* pos32, double* part,
                        int64_t* flags, hipStream_t stream)
 {
-    MD_HIP(launch_fill_i32((int32_t*)flags, 0, 2, stream), "md_forces/flags");
+    TileIo keys;
+    keys.order = cells->sorted ? nullptr : cells->order;
+    if (keys.order && !list->half && p->n >= kSpreadMinN) keys.spread = flags + 1;
+    if (p->precision == MD_MIXED || !keys.spread)
+        MD_HIP(launch_fill_i32((int32_t*)flags, 0, 2, stream), "md_forces/flags");
+    else
+        MD_HIP(launch_spread(c.g, cells->cell_xyz, flags, flags + 1, stream), "md_forces/flags");
     if (p->precision == MD_MIXED)
-        MD_HIP(launch_ref_copy(c.g, pos, cells->cell_xyz, nullptr, pos32, stream), "md_forces/pos32");
+        MD_HIP(launch_ref_copy(c.g, pos, cells->cell_xyz, nullptr, pos32, keys.spread ? flags + 1 : nullptr, stream),
+               "md_forces/pos32");
     else
         pos32 = nullptr;
     ForceOut out;
     out.force = force;
     out.part = pe_w ? part : nullptr;
     out.flags = flags;
-    TileIo keys;
-    keys.order = cells->sorted ? nullptr : cells->order;
     MD_HIP(launch_forces(c.g, c.lj, p->precision, pos, pos32, cells->cell_xyz, *list, out, stream, keys),
            "md_forces");
     if (pe_w)
@@ -669,12 +679,13 @@ static int rebuild(const Ctx& c, const md_params* p, md_state* st, bool allow_re
         st->resorts += 1;
     } else {
         MD_HIP(launch_ref_copy(c.g, st->pos, st->cells.cell_xyz, st->pos_ref,
-                               p->precision == MD_MIXED ? st->pos32 : nullptr, s),
+                               p->precision == MD_MIXED ? st->pos32 : nullptr, err + 1, s),
                "rebuild/ref");
     }
     int rc = build_list(c, p, st, tiled, true, T, F, s);
     if (rc != MD_OK) return rc;
     if ((rc = wait_flags(c, st, F, s, f, false)) != MD_OK) return rc;
+    if (!resort) st->slot_spread = (int32_t)f[5];
     if (st->list_tiled) {
         if (f[11] > tile_stage_cap(p->precision)) {
             timer_collect(T);
@@ -687,32 +698,16 @@ static int rebuild(const Ctx& c, const md_params* p, md_state* st, bool allow_re
     return MD_OK;
 }
 
-// Slot lists of a state whose slots are close to the cell order, because it
-// re-sorted a few rebuilds ago: the passes walk them as they lie, with coalesced
-// keys.  Force pass, us, 2.1 million particles, slots as they lie / cell order, at
-// 20 rebuilds after the re-sort, 56, 93 and 149: FP64 383 / 389, 503 / 499, 579 /
-// 551, 665 / 600; mixed 242 / 270, 278 / 353, 313 / 397, 359 / 444.  A mixed state
-// that never re-sorts is walked as it lies, too, where its local coordinates
-// exceed an XCD's 4 MB of L2: its inputs usually come in some spatial order (20
-// steps of 1 million in lattice order 5.15 ms, in cell order 5.67; 25 of 95,000
-// 1.21 and 1.14; FP64, 20 of 500,000: 3.8 and 3.1).
-static bool near_cell_order(const md_params* p, const md_state* st)
-{
-    const bool mixed = p->precision == MD_MIXED;
-    if (p->resort_every <= 0) return mixed && p->n > 262144;
-    const int64_t most = mixed ? 150 : 48;   // rebuilds
-    return st->resorts > 0 && st->rebuilds > 0 && (st->rebuilds - 1) % p->resort_every < most;
-}
-
-static TileIo tile_io(const md_params* p, const md_state* st)
+// step: of a force pass that takes the step, too
+static TileIo tile_io(const md_params* p, const md_state* st, bool step)
 {
     TileIo t;
     if (st->list_tiled) {
         t.start = st->cells.start;
         t.count = st->cells.count;
         t.stage = st->tile_stage;
-    } else {
-        t.order = st->cells.sorted || near_cell_order(p, st) ? nullptr : st->cells.order;
+    } else if (!st->cells.sorted && st->slot_spread > walk_spread(p->precision, step)) {
+        t.order = st->cells.order;
     }
     return t;
 }
@@ -790,7 +785,7 @@ static bool flags_arrived(const md_state* st, const Flags& F, int64_t out[16])
 }
 
 // Wait for the words of the last gather: list status [0..3], cell-grid
-// error flags [4..5], force flags [6], max squared displacement bits [7], ...
+// error flags [4], order of the slots [5], force flags [6], max squared displacement bits [7], ...
 static int wait_flags(const Ctx& c, md_state* st, Flags& F, hipStream_t s, int64_t out[16], bool last)
 {
     constexpr auto kPoll = std::chrono::microseconds(500);   // then leave the processor to others
@@ -834,7 +829,7 @@ static int force_eval(const Ctx& c, const md_params* p, md_state* st, bool energ
     out.flags = st->flags;
     tick(T, MD_T_FORCE, 0, s);
     MD_HIP(launch_forces(c.g, c.lj, p->precision, st->pos, p->precision == MD_MIXED ? st->pos32 : nullptr,
-                         st->cells.cell_xyz, st->list, out, s, tile_io(p, st)),
+                         st->cells.cell_xyz, st->list, out, s, tile_io(p, st, false)),
            "forces");
     tick(T, MD_T_FORCE, 1, s);
     return MD_OK;
@@ -1106,7 +1101,7 @@ static int step_runs(const Ctx& c, const md_params* p, md_state* st, int64_t nst
             rio.gate = gate;
             rio.idx = (int32_t)b;
             rio.thr2 = thr2;
-            const bool records = traj && step_records(p->precision, st->list, tile_io(p, st));
+            const bool records = traj && step_records(p->precision, st->list, tile_io(p, st, true));
             if (traj && !records)
                 MD_HIP(launch_record(c.g, P, st->id, traj + 4 * c.g.n * (done + b), s, rio), "step/record");
             StepIo io;
@@ -1129,7 +1124,7 @@ static int step_runs(const Ctx& c, const md_params* p, md_state* st, int64_t nst
             io.dt = p->dt;
             io.drift = !last;
             io.track_speed = false;
-            io.tile = tile_io(p, st);
+            io.tile = tile_io(p, st, true);
             io.run = rio;
             tick(T, MD_T_FORCE, 0, s);
             MD_HIP(launch_force_step(c.g, c.lj, p->precision, io, s), "step/force");
@@ -1283,7 +1278,7 @@ static int step_loop(const md_params* p, md_state* st, int64_t nsteps, int64_t s
         io.dt = p->dt;
         io.drift = !last;
         io.track_speed = p->rebuild_rule == MD_REBUILD_DUTC_LDC;
-        io.tile = tile_io(p, st);
+        io.tile = tile_io(p, st, true);
         if (!last) MD_HIP(clear_maxima(c, st, s), "step/maxd2");
         tick(T, MD_T_FORCE, 0, s);
         MD_HIP(launch_force_step(c.g, c.lj, p->precision, io, s), "step/force");

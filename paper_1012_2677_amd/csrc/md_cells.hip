@@ -570,12 +570,59 @@ hipError_t launch_pack(const Geo& g, const double* q, double* pos, hipStream_t s
     return hipGetLastError();
 }
 
+// ---- order of the slots ------------------------------------------------------
+// By one block: how far apart in space slots lie that follow one another, as the
+// squared distance of their cells (periodic, at most 64), summed over
+// kSpreadSamples pairs spread over the slots.
+__device__ void sample_spread(const Geo& g, const int32_t* __restrict__ cell_xyz, int64_t* out)
+{
+    __shared__ int s_sum[kStreamBlock / 64];
+    auto gap = [](int a, int b, int nc) {
+        const int d = abs(a - b);
+        return min(d, nc - d);
+    };
+    int sum = 0;
+#pragma unroll
+    for (int t = 0; t < kSpreadSamples / kStreamBlock; ++t) {
+        const int64_t i = (int64_t)(t * kStreamBlock + (int)threadIdx.x) * (g.n - 1) / kSpreadSamples;
+        const int32_t a = cell_xyz[i], b = cell_xyz[i + 1 < g.n ? i + 1 : i];
+        const int dx = gap(a & 1023, b & 1023, g.nc[0]), dy = gap((a >> 10) & 1023, (b >> 10) & 1023, g.nc[1]);
+        const int dz = gap((a >> 20) & 1023, (b >> 20) & 1023, g.nc[2]);
+        sum += min(dx * dx + dy * dy + dz * dz, 64);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        sum = 0;
+        for (int w = 0; w < kStreamBlock / 64; ++w) sum += s_sum[w];
+        out[0] = sum;
+    }
+}
+
+// the same, and a flag word cleared
+__global__ __launch_bounds__(kStreamBlock) void k_spread(Geo g, const int32_t* __restrict__ cell_xyz,
+                                                         int64_t* __restrict__ flag, int64_t* __restrict__ out)
+{
+    if (threadIdx.x == 0) flag[0] = 0;
+    sample_spread(g, cell_xyz, out);
+}
+
+hipError_t launch_spread(const Geo& g, const int32_t* cell_xyz, int64_t* flag, int64_t* out, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_spread, dim3(1), dim3(kStreamBlock), 0, s, g, cell_xyz, flag, out);
+    return hipGetLastError();
+}
+
 // ---- reference positions (and local coordinates) without a re-sort ----------
+// spread: the order of the slots, too, by the first block (or nullptr)
 __global__ __launch_bounds__(kStreamBlock) void k_ref_copy(Geo g, const double4* __restrict__ pos,
                                                            const int32_t* __restrict__ cell_xyz,
                                                            double* __restrict__ pos_ref,
-                                                           float4* __restrict__ pos32)
+                                                           float4* __restrict__ pos32, int64_t* __restrict__ spread)
 {
+    if (spread && blockIdx.x == 0) sample_spread(g, cell_xyz, spread);
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= g.n) return;
     const int64_t n = g.n;
@@ -615,10 +662,10 @@ hipError_t launch_record(const Geo& g, const double* pos, const int32_t* id, dou
 }
 
 hipError_t launch_ref_copy(const Geo& g, const double* pos, const int32_t* cell_xyz, double* pos_ref,
-                           float* pos32, hipStream_t s)
+                           float* pos32, int64_t* spread, hipStream_t s)
 {
     hipLaunchKernelGGL(k_ref_copy, dim3((unsigned)ceil_div(g.n, kStreamBlock)), dim3(kStreamBlock), 0, s,
-                       g, (const double4*)pos, cell_xyz, pos_ref, (float4*)pos32);
+                       g, (const double4*)pos, cell_xyz, pos_ref, (float4*)pos32, spread);
     return hipGetLastError();
 }
 

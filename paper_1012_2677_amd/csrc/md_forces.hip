@@ -3,16 +3,16 @@
 // registers while its row is walked), optionally fused with the velocity-Verlet
 // kicks and drift that consume the force (Sec. 4.5 integrator).
 //
-// Work layout.  A wave owns 64 consecutive keys of the cell order (whatever the
-// order of the slots, so that keys walked together share their partners in
-// the caches: mixed with energy, 1.15 million particles in random slot order
-// 752 us in slot order, 320 in cell order): lane L owns key base + L for
-// everything that is per key (row bounds, own coordinates, the force it ends
-// with and the integrator epilogue, coalesced when the slots are in cell
-// order).  The pair work runs in 8 rounds (fewer, with as many fewer keys, in
-// small systems): in round r the 8 lanes of group q (lanes 8q .. 8q+7) walk the
-// row of key base + 8r + q together, lane j of the group taking entries j, j+8,
-// ... so each group reads its row as one contiguous run and a round covers 8
+// Work layout.  A wave owns 64 consecutive keys: of the slots as they lie where
+// consecutive ones are close in space (walk_spread), else of the cell order, so
+// that keys walked together share their partners in the caches (mixed with
+// energy, 1.15 million particles in random slot order: 752 us as they lie, 320 in
+// cell order).  Lane L owns key base + L for everything that is per key (row
+// bounds, own coordinates, the force it ends with and the integrator epilogue,
+// coalesced when the keys are walked as they lie).  The pair work runs in 8
+// rounds (fewer, with as many fewer keys, in small systems): in round r the 8
+// lanes of group q (lanes 8q .. 8q+7) walk the row of key base + 8r + q
+// together, lane j of the group taking entries j, j+8, ... so each group reads its row as one contiguous run and a round covers 8
 // consecutive keys (consecutive rows; partners in the same few cells).  The
 // wave walks the 8 rows of a round in lockstep up to the longest (a
 // wave-uniform bound), U entries per lane at a time: U index loads, then U
@@ -79,11 +79,21 @@ struct PairArgs {
     int32_t tc, nt;            // tiled: cells per tile along z, tiles per column
     RunIo run;                 // step passes: their run of queued steps
     int32_t max_slots;         // slots that the block maxima are spread over
-    const int32_t* order;      // slot lists: slots in cell order (nullptr: they are in it)
+    const int32_t* order;      // slot lists: slots in cell order (nullptr: walked as they lie)
+    const int64_t* spread;     // given: as they lie, too, if *spread is at most spread_most
+    int32_t spread_most;
     int32_t rounds;            // slot lists: rounds of 8 keys per wave
     const int32_t* id;         // FP64 slot lists: particle of each slot and the frame that
     double4* frame;            // takes the step's positions by particle (or nullptr)
 };
+
+// Key at a place of the walk of a slot list.
+__device__ __forceinline__ int64_t key_at(const PairArgs& a, int64_t place)
+{
+    if (!a.order) return place;
+    const int64_t key = a.order[place];
+    return a.spread && a.spread[0] <= a.spread_most ? place : key;
+}
 
 // Keys [kb, ke) of logical block b of a half-list pass: a chunk of kForceBlock
 // consecutive slots.
@@ -335,7 +345,7 @@ __global__ __launch_bounds__(kForceBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_fp64(
     if (a.run.slots) chk = run_check_load(a.run);
     const int64_t blk = xcd_remap(blockIdx.x, gridDim.x);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, sub = lane & 7, grp = lane >> 3;
-    // the block's places of the cell order: K = 8 rounds per wave
+    // the block's places of the walk: K = 8 rounds per wave
     const int K = 8 * a.rounds;
     const int64_t kb = blk * NW * K, kend = kb + NW * K < a.n ? kb + NW * K : a.n;
     const double rc2 = a.lj.rc2, A = a.lj.A, B = a.lj.B, C8 = a.lj.C8;
@@ -352,7 +362,7 @@ __global__ __launch_bounds__(kForceBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_fp64(
     const bool myvalid = lane < K && base + lane < kend;
     // lanes past the end load the last key (no branch) and get an empty row
     const int64_t place = myvalid ? base + lane : kend - 1;
-    const int64_t mykey = a.order ? a.order[place] : place;
+    const int64_t mykey = key_at(a, place);
     {
         const int64_t k = mykey;
         double4 p = a.pos[k];
@@ -468,7 +478,7 @@ __global__ __launch_bounds__(kForceBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_mixed
     __syncthreads();
     const int64_t blk = xcd_remap(blockIdx.x, gridDim.x);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, sub = lane & 7, grp = lane >> 3;
-    // the block's places of the cell order: K = 8 rounds per wave
+    // the block's places of the walk: K = 8 rounds per wave
     const int K = 8 * a.rounds;
     const int64_t kb = blk * NW * K, kend = kb + NW * K < a.n ? kb + NW * K : a.n;
     const float rc2 = (float)a.lj.rc2, A = (float)a.lj.A, B = (float)a.lj.B, C8 = (float)a.lj.C8;
@@ -485,7 +495,7 @@ __global__ __launch_bounds__(kForceBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_mixed
     const bool myvalid = lane < K && base + lane < kend;
     // lanes past the end load the last key (no branch) and get an empty row
     const int64_t place = myvalid ? base + lane : kend - 1;
-    const int64_t mykey = a.order ? a.order[place] : place;
+    const int64_t mykey = key_at(a, place);
     {
         const int64_t k = mykey;
         float4 l = a.pos32[k];
@@ -1305,6 +1315,8 @@ hipError_t launch_forces(const Geo& g, const LJ& lj, int precision, const double
     a.start = tio.start;
     a.count = tio.count;
     a.order = tio.order;
+    a.spread = tio.spread;
+    a.spread_most = walk_spread(precision, false);
     a.force = out.force;
     a.part_pw = out.part;
     a.flags = out.flags;

@@ -393,8 +393,35 @@ hipError_t launch_pack(const Geo& g, const double* q, double* pos, hipStream_t s
 // (nothing when the run has stopped)
 hipError_t launch_record(const Geo& g, const double* pos, const int32_t* id, double* frame, hipStream_t s,
                          const RunIo& run = RunIo());
+// spread: also the order of the slots, as launch_spread (or nullptr)
 hipError_t launch_ref_copy(const Geo& g, const double* pos, const int32_t* cell_xyz, double* pos_ref,
-                           float* pos32, hipStream_t s);
+                           float* pos32, int64_t* spread, hipStream_t s);
+// The order of the slots: out[0] = the sum over kSpreadSamples pairs of
+// consecutive slots of the squared distance of their cells, each at most 64.
+// Also flag[0] = 0.
+hipError_t launch_spread(const Geo& g, const int32_t* cell_xyz, int64_t* flag, int64_t* out, hipStream_t s);
+// The slot-list passes walk their keys as the slots lie where this sum is at most
+// walk_spread, else in cell order.  As the slots lie the keys' own streams are
+// coalesced, in cell order the partners are near one another in the caches.
+// Time as the slots lie over time in cell order, of 2 queued steps / of an energy
+// pass, by the mean squared distance of consecutive slots (0.1 in cell order, 0.75
+// in fcc lattice order, then as the particles diffuse, up to 63 at random):
+//            1.05 million              4 million               300,000
+//   FP64     0.7 0.925 / 1.00     0.75 0.89 / 0.95     0.75 1.00 / 1.01
+//            1.1 0.98 / 1.03      1.1  0.96 / 1.07     1.1  1.03 / 1.08
+//            1.4 1.01 / 1.10      1.5  1.03 / 1.17     1.5  1.08 / 1.15
+//            63  1.60 / 2.11      64   1.68 / 2.17     62   1.45 / 1.89
+//   mixed    0.7 0.90 / 1.01      0.75 0.86 / 1.00     0.75 0.98 / 1.00
+//            1.4 0.88 / 1.02      1.5  0.85 / 1.05     1.5  0.98 / 1.08
+//            2.5 0.89 / 1.13      2.5  0.88 / 1.16     2.5  1.01 / 1.16
+//            21  0.99 / 1.11      21   1.05 / 1.24     21   1.08 / 1.17
+//            63  1.51 / 2.19      64   1.75 / 2.46     62   1.00 / 1.45
+// (20,000 to 260,000 in lattice or cell order: 25 steps 0.95 to 0.99.)
+constexpr int kSpreadSamples = 1024;
+constexpr int32_t walk_spread(int precision, bool step)
+{
+    return (int32_t)(kSpreadSamples * (precision == MD_MIXED ? (step ? 8.0 : 1.4) : (step ? 1.25 : 1.0)));
+}
 
 // md_pairlist.hip
 // tiled: write 16-bit entries that index the staged copy of the key's tile
@@ -430,12 +457,13 @@ struct ForceOut {
 };
 // Tiled lists need cells (start / count) and the largest staged count
 // (tile_stage); tile_stage = 0 selects the list of slot entries, whose keys are
-// walked in cell order (order: the slots in it, nullptr when they are in it).
+// walked in cell order (order: the slots in it) or, order = nullptr, as they lie.
 struct TileIo {
     const int32_t* start = nullptr;
     const int32_t* count = nullptr;
     int32_t stage = 0;
     const int32_t* order = nullptr;
+    const int64_t* spread = nullptr;   // given: order counts only if *spread > walk_spread (md_forces)
 };
 hipError_t launch_forces(const Geo& g, const LJ& lj, int precision, const double* pos,
                          const float* pos32, const int32_t* cell_xyz, const md_pairlist& list,
