@@ -87,12 +87,23 @@ struct PairArgs {
     double4* frame;            // takes the step's positions by particle (or nullptr)
 };
 
-// Key at a place of the walk of a slot list.
-__device__ __forceinline__ int64_t key_at(const PairArgs& a, int64_t place)
+// Waves per SIMD that the registers of the slot-list passes must leave room for.
+// Left alone, the mixed step pass takes 107 VGPRs and runs 4 (4 million as the
+// slots lie: 432 us, bounded 417), the FP64 ones up to 101.  Where a bound of 6 or
+// 7 costs spills or a tighter schedule it is left at what the pass takes (FP64
+// kick, 4 million: 638 us at 5 waves, 684 at 6).
+template <bool ENERGY, int MODE, bool MIXED>
+constexpr int slot_waves()
 {
-    if (!a.order) return place;
-    const int64_t key = a.order[place];
-    return a.spread && a.spread[0] <= a.spread_most ? place : key;
+    if (MIXED) return MODE == MODE_KKD ? (ENERGY ? 4 : 5) : (ENERGY ? 5 : (MODE == MODE_FORCE ? 7 : 6));
+    return 5;
+}
+
+// The slots in the order that a slot list is walked in, or nullptr: as they lie.
+// (At the top of a kernel, before any store: a scalar load.)
+__device__ __forceinline__ const int32_t* walk_order(const PairArgs& a)
+{
+    return a.spread && a.spread[0] <= a.spread_most ? nullptr : a.order;
 }
 
 // Keys [kb, ke) of logical block b of a half-list pass: a chunk of kForceBlock
@@ -334,12 +345,13 @@ __device__ __forceinline__ void integrate_key(const PairArgs& a, int64_t k, doub
 }
 
 template <int U, bool ENERGY, int MODE, bool VMAX>
-__global__ __launch_bounds__(kForceBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_fp64(PairArgs a)
+__global__ __launch_bounds__(kForceBlock, (slot_waves<ENERGY, MODE, false>())) void k_pairs_fp64(PairArgs a)
 {
     constexpr int NW = kForceBlock / 64;
     __shared__ double4 s_p[NW][64];     // own position, .w = 1 if the key needs minimum images
     __shared__ int64_t s_off[NW][64];
     __shared__ int32_t s_cnt[NW][64];
+    const int32_t* order = walk_order(a);
     if (!a.run.slots && a.run.idx > 0 && a.run.gate[0]) return;
     RunCheck chk;
     if (a.run.slots) chk = run_check_load(a.run);
@@ -362,7 +374,7 @@ __global__ __launch_bounds__(kForceBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_fp64(
     const bool myvalid = lane < K && base + lane < kend;
     // lanes past the end load the last key (no branch) and get an empty row
     const int64_t place = myvalid ? base + lane : kend - 1;
-    const int64_t mykey = key_at(a, place);
+    const int64_t mykey = order ? order[place] : place;
     {
         const int64_t k = mykey;
         double4 p = a.pos[k];
@@ -458,13 +470,14 @@ __global__ __launch_bounds__(kForceBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_fp64(
 }
 
 template <int U, bool ENERGY, int MODE, bool VMAX>
-__global__ __launch_bounds__(kForceBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_mixed(PairArgs a)
+__global__ __launch_bounds__(kForceBlock, (slot_waves<ENERGY, MODE, true>())) void k_pairs_mixed(PairArgs a)
 {
     constexpr int NW = kForceBlock / 64;
     __shared__ float4 s_shift[32];
     __shared__ float4 s_l[NW][64];
     __shared__ int64_t s_off[NW][64];
     __shared__ int32_t s_cnt[NW][64];
+    const int32_t* order = walk_order(a);
     if (!a.run.slots && a.run.idx > 0 && a.run.gate[0]) return;
     RunCheck chk;
     if (a.run.slots) chk = run_check_load(a.run);
@@ -495,7 +508,7 @@ __global__ __launch_bounds__(kForceBlock, MD_PAIR_MIN_BLOCKS) void k_pairs_mixed
     const bool myvalid = lane < K && base + lane < kend;
     // lanes past the end load the last key (no branch) and get an empty row
     const int64_t place = myvalid ? base + lane : kend - 1;
-    const int64_t mykey = key_at(a, place);
+    const int64_t mykey = order ? order[place] : place;
     {
         const int64_t k = mykey;
         float4 l = a.pos32[k];
