@@ -40,7 +40,8 @@ TIMER_NAMES = ["force", "integrate", "bin", "resort", "build", "reduce", "check"
 
 EXPORTED = ["md_cell_dims", "md_workspace_bytes", "md_pack_positions", "md_bin_cells", "md_resort", "md_build_pairlist",
             "md_forces", "md_prepare", "md_step", "md_energy", "md_hvp", "md_adjoint_kick", "md_param_grad",
-            "md_ldc_check", "md_last_error", "md_hbm_probe", "md_forces_noalloc", "md_step_record"]
+            "md_ldc_check", "md_last_error", "md_hbm_probe", "md_forces_noalloc", "md_step_record",
+            "md_adjoint_workspace_bytes"]
 MD_NOALLOC_MAX_N = 1 << 20
 
 MD_PROBE_READ, MD_PROBE_COPY, MD_PROBE_TRIAD, MD_PROBE_NT = 0, 1, 2, 4
@@ -105,6 +106,7 @@ def lib():
     sig = {
         "md_cell_dims": (C.c_int, [P(MdParams), P(C.c_int32)]),
         "md_workspace_bytes": (C.c_size_t, [P(MdParams)]),
+        "md_adjoint_workspace_bytes": (C.c_size_t, [P(MdParams)]),
         "md_pack_positions": (C.c_int, [P(MdParams), vp, vp, vp]),
         "md_bin_cells": (C.c_int, [P(MdParams), vp, P(MdCells), vp, C.c_size_t, vp]),
         "md_resort": (C.c_int, [P(MdParams), P(MdState), vp]),
@@ -153,6 +155,10 @@ def md_cell_dims(params: MdParams):
 
 def md_workspace_bytes(params: MdParams) -> int:
     return int(lib().md_workspace_bytes(C.byref(params)))
+
+
+def md_adjoint_workspace_bytes(params: MdParams) -> int:
+    return int(lib().md_adjoint_workspace_bytes(C.byref(params)))
 
 
 def md_pack_positions(params, q, pos, stream):

@@ -40,7 +40,7 @@ class Field:
                                   precision="fp64", resort_every=0)
         self.grid = Grid(self.params, self.device)
         self.plist = PairList(self.params, self.grid.ncell, self.device)
-        self.ws = Workspace(self.params, self.device)
+        self.ws = Workspace(self.params, self.device, adjoint=True)
         self._own_pos = torch.empty((self.n, 4), dtype=torch.float64, device=self.device)
         self.pos = self._own_pos
         self.out2 = torch.empty(2, dtype=torch.float64, device=self.device)

@@ -179,8 +179,6 @@ WsLayout ws_layout(const Geo& g, const md_params& p)
     L.part_b = off;    off = align256(off + sizeof(double) * (size_t)(np > L.nbi ? np : L.nbi));
     // local coordinates of md_forces in mixed precision only
     L.pos32 = off;     off = align256(off + (p.precision == MD_MIXED ? 16 * (size_t)n : 0));
-    L.has_rec = p.precision == MD_FP64 && p.resort_every == 0 && n >= kRecMinN;
-    L.rec = off;       off = align256(off + (L.has_rec ? 48 * (size_t)n : 0));
     L.red = off;       off = align256(off + sizeof(int64_t) * 2 * 1024);
     L.ldc = off;       off = align256(off + sizeof(int32_t) * (size_t)(ldc_max > 0 ? ldc_max : 1));
     L.scal = off;      off = align256(off + sizeof(int64_t) * 32);
@@ -188,6 +186,8 @@ WsLayout ws_layout(const Geo& g, const md_params& p)
     L.mx = off;        off = align256(off + sizeof(int64_t) * 2 * kMaxSlots * kMaxSlotStride);
     L.tile_used = off; off = align256(off + sizeof(int32_t) * (size_t)(g.ntile > 0 ? g.ntile : 1));
     L.total = off;
+    L.rec = off;       off = align256(off + (n >= kRecMinN ? 48 * (size_t)n : 0));
+    L.total_rec = off;
     return L;
 }
 
@@ -352,6 +352,13 @@ size_t md_workspace_bytes(const md_params* p)
     return ws_layout(make_geo(*p, nc), *p).total;
 }
 
+size_t md_adjoint_workspace_bytes(const md_params* p)
+{
+    int32_t nc[3];
+    if (check_params(p, nc) != MD_OK) return 0;
+    return ws_layout(make_geo(*p, nc), *p).total_rec;
+}
+
 int md_pack_positions(const md_params* p, const double* q, double* pos, hipStream_t stream)
 {
     Ctx c;
@@ -510,9 +517,10 @@ int md_forces_noalloc(const md_params* p, const double* pos, const md_cells* cel
                        (int64_t*)(w + kNoAllocPos32 + kNoAllocPart), stream);
 }
 
-static double* adj_records(const Ctx& c, void* ws)
+// Room for the records of an adjoint pass, where the caller's workspace has it.
+static double* adj_records(const Ctx& c, void* ws, size_t ws_bytes)
 {
-    return c.W.has_rec ? (double*)((char*)ws + c.W.rec) : nullptr;
+    return c.W.total_rec > c.W.total && ws_bytes >= c.W.total_rec ? (double*)((char*)ws + c.W.rec) : nullptr;
 }
 
 int md_hvp(const md_params* p, const double* pos, const md_cells* cells, const md_pairlist* list,
@@ -526,7 +534,9 @@ int md_hvp(const md_params* p, const double* pos, const md_cells* cells, const m
     if ((rc = check_slot_list(c, list, false)) != MD_OK) return rc;
     if ((rc = check_ws(c, ws, ws_bytes)) != MD_OK) return rc;
     double* part = dparam ? (double*)((char*)ws + c.W.part_a) : nullptr;
-    MD_HIP(launch_hvp(c.g, c.lj, pos, *cells, *list, u, Hu, part, adj_records(c, ws), stream), "md_hvp");
+    // (without dparam the call leaves the workspace alone)
+    double* rec = dparam ? adj_records(c, ws, ws_bytes) : nullptr;
+    MD_HIP(launch_hvp(c.g, c.lj, pos, *cells, *list, u, Hu, part, rec, stream), "md_hvp");
     if (dparam) MD_HIP(launch_reduce_pair(part, c.W.nbf, 1.0, 1.0, dparam, stream), "md_hvp/reduce");
     return MD_OK;
 }
@@ -568,7 +578,8 @@ int md_adjoint_kick(const md_params* p, const double* pos, const md_cells* cells
     k.cU = coef[4];
     k.dt = p->dt;
     double* part = (double*)((char*)ws + c.W.part_a);
-    MD_HIP(launch_adjoint_kick(c.g, c.lj, pos, *cells, *list, u, out, u_out, k, part, adj_records(c, ws), stream),
+    MD_HIP(launch_adjoint_kick(c.g, c.lj, pos, *cells, *list, u, out, u_out, k, part, adj_records(c, ws, ws_bytes),
+                               stream),
            "md_adjoint_kick");
     MD_HIP(launch_reduce_pair(part, c.W.nbf, 1.0, 1.0, acc, stream, true), "md_adjoint_kick/reduce");
     return MD_OK;

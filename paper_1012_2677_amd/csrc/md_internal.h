@@ -146,7 +146,6 @@ struct WsLayout {
     size_t part_a;     // double[2*nbf]  per-block partial sums (force kernels)
     size_t part_b;     // double[nbi]    per-block partial sums (streaming kernels)
     size_t pos32;      // float4[n]      mixed-mode local coordinates (md_forces; empty in FP64)
-    size_t rec;        // double[6 n]    records of the adjoint passes (FP64 without re-sorts; else empty)
     size_t red;        // int64[2*1024]  partials of the list statistics
     size_t ldc;        // int32[ldc_max] members of the large-displacement check
     size_t scal;       // int64[32]      small device scalars (layout in md_api.hip)
@@ -154,7 +153,8 @@ struct WsLayout {
     size_t mx;         // int64[2][kMaxSlots * kMaxSlotStride]  block maxima of d2 and v2
     size_t tile_used;  // int32[ntile]   entries taken in each tile's pooled block (tiled list build)
     size_t total;
-    bool has_rec;      // the adjoint passes run on slot lists, which a re-sorting state does not keep
+    size_t rec;        // double[6 n]    records of the adjoint passes, past the rest (total where they use none)
+    size_t total_rec;
     int64_t nbs;       // scan blocks
     int64_t nbf;       // adjoint-kernel blocks (kKeysPerBlock keys each)
     int64_t nbi;       // streaming-kernel blocks
