@@ -670,7 +670,9 @@ static int rebuild(const Ctx& c, const md_params* p, md_state* st, bool allow_re
     // what the passes below count into, in one launch
     ClearList clear;
     if (bin_clears_counts(c.g)) clear.add(st->cells.count, c.g.ncell);
-    build_clears(c.g, st->list, st->ws, c.W, tiled, (unsigned long long*)((char*)st->ws + c.W.tmax), clear);
+    // (a list without room for the layout is not built and keeps its status)
+    if (st->list.capacity >= list_words(c, &st->list, tiled))
+        build_clears(c.g, st->list, st->ws, c.W, tiled, (unsigned long long*)((char*)st->ws + c.W.tmax), clear);
     MD_HIP(launch_clear(clear, s), "rebuild/clear");
     MD_HIP(launch_bin(c.g, st->pos, st->cells, st->ws, c.W, err, s), "rebuild/bin");
     tick(T, MD_T_BIN, 1, s);
