@@ -245,9 +245,12 @@ __global__ __launch_bounds__(kStreamBlock) void k_scatter(int64_t n, const int32
 // after another (sort_by_cell).  Few cells per block on small grids, which
 // otherwise have too few blocks (28^3 cells at 11.7 particles, 64, 32, 16, 8 per
 // block: 6.4, 5.1, 4.1, 5.7 us; an insertion sort by a thread per cell of 256
-// 17.5), more on large ones, where a block's three waits cost more (142^3 cells:
-// 16, 32, 64 per block 211, 167, 127 us; the insertion sort 117).
+// 17.5), more on larger ones, where a block's three waits cost more (71^3 cells,
+// 128 per block 21 us, the insertion sort 23.5; 142^3 cells: 16, 32, 64, 128 per
+// block 211, 167, 127, 118 us, the insertion sort 99, which grids of more than
+// kSortManyCells therefore take).
 constexpr int64_t kSortFewCells = 131072;
+constexpr int64_t kSortManyCells = 1048576;
 constexpr int kSortLds = 4096;   // slots of one block's cells sorted in LDS
 
 // The same for the cells of a block that are too crowded together (a cutoff of
@@ -335,6 +338,45 @@ __global__ __launch_bounds__(kStreamBlock) void k_sort_cells(int64_t ncell, cons
         for (int q = q0; q < q1; ++q) r += s_o[q] < x;
         order[b0 + q0 + r] = x;
     }
+}
+
+// A thread per cell, which sorts its slots in LDS by insertion (the groups that
+// the scatter leaves are nearly in order).
+__device__ __forceinline__ void insertion_sort(int32_t* v, int32_t len)
+{
+    for (int32_t k = 1; k < len; ++k) {
+        const int32_t x = v[k];
+        int32_t p = k;
+        bool more = true;
+        while (more) {
+            const int32_t y = v[p - 1];
+            more = y > x;
+            if (more) v[p] = y;
+            p -= more ? 1 : 0;
+            more &= p > 0;
+        }
+        v[p] = x;
+    }
+}
+
+__global__ __launch_bounds__(kStreamBlock) void k_sort_cells_by_thread(int64_t ncell, const int32_t* __restrict__ start,
+                                                                       int32_t* __restrict__ order,
+                                                                       int32_t* __restrict__ tmp)
+{
+    __shared__ int32_t s_o[kSortLds];
+    const int64_t c0 = (int64_t)blockIdx.x * kStreamBlock;
+    const int64_t c1 = c0 + kStreamBlock < ncell ? c0 + kStreamBlock : ncell;
+    const int64_t c = c0 + threadIdx.x;
+    const int32_t b0 = start[c0], len = start[c1] - b0;
+    if (len > kSortLds) {
+        sort_by_cell(c0, (int)(c1 - c0), start, order, tmp, s_o);
+        return;
+    }
+    for (int32_t t = threadIdx.x; t < len; t += kStreamBlock) s_o[t] = order[b0 + t];
+    __syncthreads();
+    if (c < c1) insertion_sort(s_o + (start[c] - b0), start[c + 1] - start[c]);
+    __syncthreads();
+    for (int32_t t = threadIdx.x; t < len; t += kStreamBlock) order[b0 + t] = s_o[t];
 }
 
 // ---- the same for small systems in one block --------------------------------
@@ -482,7 +524,10 @@ hipError_t launch_bin(const Geo& g, const double* pos, const md_cells& cells, vo
                            g.ncell, (const int32_t*)cells.start, cells.order, rank);   // (ranks are read)
     };
     if (g.ncell <= kSortFewCells) sort(std::integral_constant<int, 16>());
-    else sort(std::integral_constant<int, 128>());
+    else if (g.ncell <= kSortManyCells) sort(std::integral_constant<int, 128>());
+    else
+        hipLaunchKernelGGL(k_sort_cells_by_thread, dim3((unsigned)ceil_div(g.ncell, kStreamBlock)), dim3(kStreamBlock),
+                           0, s, g.ncell, (const int32_t*)cells.start, cells.order, rank);
     return hipGetLastError();
 }
 
