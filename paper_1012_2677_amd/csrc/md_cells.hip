@@ -182,48 +182,43 @@ __global__ __launch_bounds__(kStreamBlock) void k_scan_final(const int32_t* __re
     if (blockIdx.x == 0 && threadIdx.x == 0) out[m] = bsum[nb];
 }
 
-// The same scan in one launch of one block, for grids whose counts one block
-// reads in one turn (3375 cells: 4.5 us against three launches and their gaps;
-// 28^3 cells in three turns 22 us, three launches 13).
+// The same scan in one launch of one block, for grids of up to kScanOneCells, whose
+// counts one block reads in one turn (3375 cells: 4.5 us against three launches
+// and their gaps; 28^3 cells in three turns 22 us, three launches 13).
 constexpr int kScanOneThreads = 1024;
-constexpr int kScanOneItems = 8;              // per thread and turn
+constexpr int kScanOneItems = 8;              // per thread
 constexpr int64_t kScanOneCells = kScanOneThreads * kScanOneItems;
 __global__ __launch_bounds__(kScanOneThreads) void k_scan_one(const int32_t* __restrict__ in, int m,
                                                               int32_t* __restrict__ out)
 {
     __shared__ int32_t s_wave[kScanOneThreads / 64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int32_t carry = 0;
-    for (int t0 = 0; t0 < m; t0 += kScanOneThreads * kScanOneItems) {
-        const int base = t0 + (int)threadIdx.x * kScanOneItems;
-        int32_t v[kScanOneItems], sum = 0;
+    const int base = (int)threadIdx.x * kScanOneItems;
+    int32_t v[kScanOneItems], sum = 0;
 #pragma unroll
-        for (int k = 0; k < kScanOneItems; ++k) v[k] = base + k < m ? in[base + k] : 0;
+    for (int k = 0; k < kScanOneItems; ++k) v[k] = base + k < m ? in[base + k] : 0;
 #pragma unroll
-        for (int k = 0; k < kScanOneItems; ++k) sum += v[k];
-        int32_t x = sum;
+    for (int k = 0; k < kScanOneItems; ++k) sum += v[k];
+    int32_t x = sum;
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int32_t y = __shfl_up(x, o, 64);
-            if (lane >= o) x += y;
-        }
-        if (lane == 63) s_wave[wave] = x;
-        __syncthreads();
-        int32_t run = carry + x - sum, tot = 0;
-        for (int w = 0; w < kScanOneThreads / 64; ++w) {
-            const int32_t t = s_wave[w];
-            if (w < wave) run += t;
-            tot += t;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < kScanOneItems; ++k) {
-            if (base + k < m) out[base + k] = run;
-            run += v[k];
-        }
-        carry += tot;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int32_t y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
     }
-    if (threadIdx.x == 0) out[m] = carry;
+    if (lane == 63) s_wave[wave] = x;
+    __syncthreads();
+    int32_t run = x - sum, tot = 0;
+    for (int w = 0; w < kScanOneThreads / 64; ++w) {
+        const int32_t t = s_wave[w];
+        if (w < wave) run += t;
+        tot += t;
+    }
+#pragma unroll
+    for (int k = 0; k < kScanOneItems; ++k) {
+        if (base + k < m) out[base + k] = run;
+        run += v[k];
+    }
+    if (threadIdx.x == 0) out[m] = tot;
 }
 
 // ---- place + per-cell sort ---------------------------------------------------
