@@ -233,7 +233,12 @@ typedef struct md_timers {
  *   the largest squared displacement since the last build and the largest
  *   squared drift speed of the last step, reserved.
  *   flags: device int64[8]: [0] non-finite force seen, others reserved.
- *   host_scratch: host int64[16] (pinned recommended) for flag read-back.
+ *   host_scratch: host int64[16] for flag read-back, of this state alone.  In
+ *   pinned memory the device stores all 16 words there during md_prepare and
+ *   md_step while the host polls for them, sealed against a partial arrival (so
+ *   calls that overlap in time must not share the words); with ordinary memory
+ *   or NULL, and with timers, each read-back is a copy and a wait for the
+ *   stream.  A call has ended on the stream when it returns either way.
  *   ws: device workspace of ws_bytes >= md_workspace_bytes().
  *   step, rebuilds, resorts: host counters; phase: 0 = (q, v, F) at a whole
  *   step, 1 = stopped after a drift (resumed by the next md_step), 2 = arrays
@@ -401,11 +406,12 @@ int md_prepare(const md_params* p, md_state* st, hipStream_t stream);
  * energy_log[k][0..3] = (KE, PE, W, KE + PE) is written (device double
  * array; NULL to skip; sample_every <= 0 samples nothing).
  * With MD_REBUILD_HALF_SKIN and a full list the rebuild decision is taken on
- * the device: steps are queued in runs (md_params.step_run), the passes of a
- * step first read the largest displacement that the step before left and do
- * nothing once a step must rebuild, and the host waits once
- * per run and once per rebuild, resuming where the run stopped.  With
- * MD_REBUILD_DUTC_LDC or a half list it waits once per step.
+ * the device: steps are queued in runs (md_params.step_run), and once a step
+ * must rebuild, its passes and those of the run's later steps do nothing (force
+ * passes of up to 8192 blocks read the largest displacement that the step before
+ * left; before larger ones a small pass after each step sets a gate that they
+ * read).  The host waits once per run and once per rebuild, resuming where the
+ * run stopped.  With MD_REBUILD_DUTC_LDC or a half list it waits once per step.
  * On MD_ERR_CAPACITY the state stops in phase 1 with st->step steps done;
  * grow the list and call md_step again.
  * MD_ERR_NONFINITE stops after the step that produced a non-finite force. */

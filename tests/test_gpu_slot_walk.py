@@ -6,7 +6,7 @@ in lattice order fall on one side of the rule, shuffled ones on the other, in
 each precision.  On either walk the fused step passes take the same steps
 whatever the host's waits, track the oracle (FP64) or the FP64 run (mixed), and
 keep energy and virial at the oracle's; md_forces, which measures for itself
-from 524,288 particles on, gives the oracle's forces and the same bits twice.
+from 2,097,152 particles on, gives the oracle's forces and the same bits twice.
 
 Tolerances: FP64 sums of up to a few hundred terms per particle, 1e-12 of their
 scale; mixed pair terms carry 2^-24 each, 1e-5 of the scale.  A mixed run's
@@ -128,9 +128,9 @@ def test_recorded_frames_on_either_walk(precision, shuffled):
 
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
 @pytest.mark.parametrize("shuffled", [False, True])
-@pytest.mark.parametrize("n", [524287, 524288, 530001])
+@pytest.mark.parametrize("n", [2097151, 2097152, 2100001])
 def test_forces_on_either_side_of_the_measured_size(ref, precision, shuffled, n):
-    q, _, L = _box(51, shuffled)        # 530,604
+    q, _, L = _box(81, shuffled)        # 2,125,764
     q = q[:n]
     s = G.Standalone(q, L, precision=precision)
     s.bin()
@@ -142,7 +142,7 @@ def test_forces_on_either_side_of_the_measured_size(ref, precision, shuffled, n)
     Fr, S, _, _, _ = ref.forces_sample(q, L, sample)
     assert G.force_error(F[sample], Fr, S) < (1e-12 if precision == "fp64" else 1e-5)
     # the other order of the same particles: the same sums in another order
-    if n == 530001:
+    if n == 2100001:
         back = np.random.default_rng(9).permutation(n) if not shuffled else np.argsort(np.floor(q[:, 0]), kind="stable")
         o = G.Standalone(q[back], L, precision=precision)
         o.bin()
@@ -151,3 +151,16 @@ def test_forces_on_either_side_of_the_measured_size(ref, precision, shuffled, n)
         assert np.allclose(pw3, pw, rtol=1e-11 if precision == "fp64" else 1e-6)
         S2 = np.maximum(np.linalg.norm(F[back], axis=1), 1.0)
         assert (np.linalg.norm(G2 - F[back], axis=1) / S2).max() < (1e-10 if precision == "fp64" else 1e-3)
+
+
+@pytest.mark.parametrize("n_fcc,shuffled", [(20, False), (20, True), (82, False)])
+def test_mixed_slot_steps_on_either_side_of_the_fold(n_fcc, shuffled):
+    # 1000 blocks check the run themselves, 8616 read the gate
+    q, v, L = _box(n_fcc, shuffled, seed=3)
+    v *= np.sqrt(1.5)
+    a = _engine(q, v, L, precision="mixed", resort_every=0)
+    a.step(14)
+    b = _engine(q, v, L, precision="mixed", resort_every=0, step_run=1)
+    b.step(14)
+    assert a.rebuilds == b.rebuilds > 1
+    assert torch.equal(a.pos, b.pos) and torch.equal(a.vel, b.vel)
