@@ -180,7 +180,8 @@ typedef struct md_cells {
  *             state whose list is tiled (16-bit entries, see md_state)
  *             capacity >= nc * cell_stride / 2 (rounded up) is enough; should
  *             such a state need slot entries, md_prepare / md_step return
- *             MD_ERR_CAPACITY with status[2] clear (grow nbr and call again)
+ *             MD_ERR_CAPACITY with status[2] clear and the last list's [0] and
+ *             [1] (grow nbr and call again)
  *   status    device int64[4]: [0] total entries, [1] largest per-cell block,
  *             [2] 1 if some cell block overflowed cell_stride (list invalid),
  *             [3] reserved.

@@ -631,8 +631,10 @@ static int build_list(const Ctx& c, const md_params* p, md_state* st, bool tiled
 {
     if (st->list.capacity < list_words(c, &st->list, tiled)) {
         // the caller gave room for 16-bit entries only; slot entries need twice
-        // as much (the list is left invalid; status[2] stays clear)
+        // as much (the list is left invalid; its overflow word, which tells this
+        // error from an overflow, is clear, also after a list that overflowed)
         st->list_valid = 0;
+        MD_HIP(launch_fill_i32((int32_t*)(st->list.status + 2), 0, 2, s), "rebuild/status");
         return fail(MD_ERR_CAPACITY, "slot entries need %lld words of nbr, capacity is %lld",
                     (long long)list_words(c, &st->list, tiled), (long long)st->list.capacity);
     }
@@ -671,7 +673,7 @@ static int rebuild(const Ctx& c, const md_params* p, md_state* st, bool allow_re
     // what the passes below count into, in one launch
     ClearList clear;
     if (bin_clears_counts(c.g)) clear.add(st->cells.count, c.g.ncell);
-    // (a list without room for the layout is not built and keeps its status)
+    // (a list without room for the layout is not built and keeps its totals)
     if (st->list.capacity >= list_words(c, &st->list, tiled))
         build_clears(c.g, st->list, st->ws, c.W, tiled, (unsigned long long*)((char*)st->ws + c.W.tmax), clear);
     MD_HIP(launch_clear(clear, s), "rebuild/clear");
