@@ -12,9 +12,9 @@
 // coalesced when the keys are walked as they lie).  The pair work runs in 8
 // rounds (fewer, with as many fewer keys, in small systems): in round r the 8
 // lanes of group q (lanes 8q .. 8q+7) walk the row of key base + 8r + q
-// together, lane j of the group taking entries j, j+8, ... so each group reads its row as one contiguous run and a round covers 8
-// consecutive keys (consecutive rows; partners in the same few cells).  The
-// wave walks the 8 rows of a round in lockstep up to the longest (a
+// together, lane j of the group taking entries j, j+8, ... so each group reads
+// its row as one contiguous run and a round covers 8 consecutive keys
+// (consecutive rows; partners in the same few cells).  The wave walks the 8 rows of a round in lockstep up to the longest (a
 // wave-uniform bound), U entries per lane at a time: U index loads, then U
 // position gathers, then U pair terms.  (FP64, 1 million keys with energy, 160
 // us: the vector cache takes 88 million look-ups, close to one a cycle.  The
