@@ -414,11 +414,12 @@ int md_build_pairlist(const md_params* p, const double* pos, const md_cells* cel
 // The force pass of md_forces and md_forces_noalloc, with its scratch given:
 // pos32 (mixed precision: float4 per particle), part (2 doubles per block of
 // the pass), one flag word (cleared here) and the word after it.  From kSpreadMinN
-// on the pass learns the order of the slots first, which costs 2 to 4 us (FP64,
-// in lattice order / at random: 2.1 million 346 -> 328 / 919 -> 921 us, 4 million
-// 623 -> 600); below it the cell order loses no more than that on ordered slots (1
-// million: 182 / 179).
-constexpr int64_t kSpreadMinN = 2097152;
+// on the pass learns the order of the slots first, which costs 2 to 4 us.  In
+// lattice order / at random, us, cell order -> measured: FP64 1 million 157 -> 153
+// / 390 -> 392, 1.7 million 263 -> 261 / 695 -> 697, 2.1 million 346 -> 328 / 919 ->
+// 921, 4 million 623 -> 600; mixed 1 million 108 -> 107 / 315 -> 318, 1.7 million
+// 170 -> 161 / 581 -> 581, 2.1 million 224 -> 213 / 760 -> 765.
+constexpr int64_t kSpreadMinN = 1572864;
 static int forces_with(const Ctx& c, const md_params* p, const double* pos, const md_cells* cells,
                        const md_pairlist* list, void* force, double* pe_w, float* pos32, double* part,
                        int64_t* flags, hipStream_t stream)

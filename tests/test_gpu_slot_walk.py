@@ -6,7 +6,7 @@ in lattice order fall on one side of the rule, shuffled ones on the other, in
 each precision.  On either walk the fused step passes take the same steps
 whatever the host's waits, track the oracle (FP64) or the FP64 run (mixed), and
 keep energy and virial at the oracle's; md_forces, which measures for itself
-from 2,097,152 particles on, gives the oracle's forces and the same bits twice.
+from 1,572,864 particles on, gives the oracle's forces and the same bits twice.
 
 Tolerances: FP64 sums of up to a few hundred terms per particle, 1e-12 of their
 scale; mixed pair terms carry 2^-24 each, 1e-5 of the scale.  A mixed run's
@@ -128,9 +128,9 @@ def test_recorded_frames_on_either_walk(precision, shuffled):
 
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
 @pytest.mark.parametrize("shuffled", [False, True])
-@pytest.mark.parametrize("n", [2097151, 2097152, 2100001])
+@pytest.mark.parametrize("n", [1572863, 1572864, 1590001])
 def test_forces_on_either_side_of_the_measured_size(ref, precision, shuffled, n):
-    q, _, L = _box(81, shuffled)        # 2,125,764
+    q, _, L = _box(74, shuffled)        # 1,620,896
     q = q[:n]
     s = G.Standalone(q, L, precision=precision)
     s.bin()
@@ -142,7 +142,7 @@ def test_forces_on_either_side_of_the_measured_size(ref, precision, shuffled, n)
     Fr, S, _, _, _ = ref.forces_sample(q, L, sample)
     assert G.force_error(F[sample], Fr, S) < (1e-12 if precision == "fp64" else 1e-5)
     # the other order of the same particles: the same sums in another order
-    if n == 2100001:
+    if n == 1590001:
         back = np.random.default_rng(9).permutation(n) if not shuffled else np.argsort(np.floor(q[:, 0]), kind="stable")
         o = G.Standalone(q[back], L, precision=precision)
         o.bin()
