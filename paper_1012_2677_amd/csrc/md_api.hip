@@ -723,7 +723,7 @@ static TileIo tile_io(const md_params* p, const md_state* st, bool step)
         t.start = st->cells.start;
         t.count = st->cells.count;
         t.stage = st->tile_stage;
-    } else if (!st->cells.sorted && st->slot_spread > walk_spread(p->precision, step)) {
+    } else if (!st->cells.sorted && st->slot_spread > walk_spread(p->precision, step, p->n)) {
         t.order = st->cells.order;
     }
     return t;

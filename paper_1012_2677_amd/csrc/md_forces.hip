@@ -100,10 +100,13 @@ constexpr int slot_waves()
 }
 
 // The slots in the order that a slot list is walked in, or nullptr: as they lie.
-// (At the top of a kernel, before any store: a scalar load.)
+// MEASURED: by the measure in memory (at the top of a kernel, before any store: a
+// scalar load; a variant, since it costs the others 0.5%).
+template <bool MEASURED>
 __device__ __forceinline__ const int32_t* walk_order(const PairArgs& a)
 {
-    return a.spread && a.spread[0] <= a.spread_most ? nullptr : a.order;
+    if (MEASURED && a.spread[0] <= a.spread_most) return nullptr;
+    return a.order;
 }
 
 // Keys [kb, ke) of logical block b of a half-list pass: a chunk of kForceBlock
@@ -344,14 +347,14 @@ __device__ __forceinline__ void integrate_key(const PairArgs& a, int64_t k, doub
     integrate_loaded<MODE, MIXED, VMAX>(a, k, load_key<MODE, MIXED>(a, k), fx, fy, fz, ke, d2, v2);
 }
 
-template <int U, bool ENERGY, int MODE, bool VMAX>
+template <int U, bool ENERGY, int MODE, bool VMAX, bool MEASURED>
 __global__ __launch_bounds__(kForceBlock, (slot_waves<ENERGY, MODE, false>())) void k_pairs_fp64(PairArgs a)
 {
     constexpr int NW = kForceBlock / 64;
     __shared__ double4 s_p[NW][64];     // own position, .w = 1 if the key needs minimum images
     __shared__ int64_t s_off[NW][64];
     __shared__ int32_t s_cnt[NW][64];
-    const int32_t* order = walk_order(a);
+    const int32_t* order = walk_order<MEASURED>(a);
     if (!a.run.slots && a.run.idx > 0 && a.run.gate[0]) return;
     RunCheck chk;
     if (a.run.slots) chk = run_check_load(a.run);
@@ -469,7 +472,7 @@ __global__ __launch_bounds__(kForceBlock, (slot_waves<ENERGY, MODE, false>())) v
     if (ENERGY || MODE == MODE_KKD) block_epilogue<ENERGY, MODE, VMAX>(a, blk, pe, w, ke, d2, v2);
 }
 
-template <int U, bool ENERGY, int MODE, bool VMAX>
+template <int U, bool ENERGY, int MODE, bool VMAX, bool MEASURED>
 __global__ __launch_bounds__(kForceBlock, (slot_waves<ENERGY, MODE, true>())) void k_pairs_mixed(PairArgs a)
 {
     constexpr int NW = kForceBlock / 64;
@@ -477,7 +480,7 @@ __global__ __launch_bounds__(kForceBlock, (slot_waves<ENERGY, MODE, true>())) vo
     __shared__ float4 s_l[NW][64];
     __shared__ int64_t s_off[NW][64];
     __shared__ int32_t s_cnt[NW][64];
-    const int32_t* order = walk_order(a);
+    const int32_t* order = walk_order<MEASURED>(a);
     if (!a.run.slots && a.run.idx > 0 && a.run.gate[0]) return;
     RunCheck chk;
     if (a.run.slots) chk = run_check_load(a.run);
@@ -1282,10 +1285,17 @@ static void launch_pairs_mode(const Geo& g, int precision, const PairArgs& a, hi
         return launch(std::false_type());
     }
     const dim3 grid((unsigned)pair_blocks(g)), block(kForceBlock);
-    if (precision == MD_MIXED)
-        hipLaunchKernelGGL((k_pairs_mixed<kForceUnroll, ENERGY, MODE, VMAX>), grid, block, 0, s, a);
-    else
-        hipLaunchKernelGGL((k_pairs_fp64<kForceUnroll64, ENERGY, MODE, VMAX>), grid, block, 0, s, a);
+    auto launch = [&](auto measured) {
+        constexpr bool M = decltype(measured)::value;
+        if (precision == MD_MIXED)
+            hipLaunchKernelGGL((k_pairs_mixed<kForceUnroll, ENERGY, MODE, VMAX, M>), grid, block, 0, s, a);
+        else
+            hipLaunchKernelGGL((k_pairs_fp64<kForceUnroll64, ENERGY, MODE, VMAX, M>), grid, block, 0, s, a);
+    };
+    if constexpr (MODE == MODE_FORCE) {
+        if (a.spread) return launch(std::true_type());
+    }
+    launch(std::false_type());
 }
 
 // Half list: clear the force array, then the pair pass with atomics.
@@ -1329,7 +1339,7 @@ hipError_t launch_forces(const Geo& g, const LJ& lj, int precision, const double
     a.count = tio.count;
     a.order = tio.order;
     a.spread = tio.spread;
-    a.spread_most = walk_spread(precision, false);
+    a.spread_most = walk_spread(precision, false, g.n);
     a.force = out.force;
     a.part_pw = out.part;
     a.flags = out.flags;

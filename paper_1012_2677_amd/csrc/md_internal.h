@@ -416,11 +416,13 @@ hipError_t launch_spread(const Geo& g, const int32_t* cell_xyz, int64_t* flag, i
 //            2.5 0.89 / 1.13      2.5  0.88 / 1.16     2.5  1.01 / 1.16
 //            21  0.99 / 1.11      21   1.05 / 1.24     21   1.08 / 1.17
 //            63  1.51 / 2.19      64   1.75 / 2.46     62   1.00 / 1.45
-// (20,000 to 260,000 in lattice or cell order: 25 steps 0.95 to 0.99.)
+// (20,000 to 260,000 in lattice or cell order: 25 steps 0.95 to 0.99.  FP64 steps
+// of 500,000: 0.98 at 0.8, 1.00 at 1.06, 1.03 at 1.4, hence the lower line there.)
 constexpr int kSpreadSamples = 1024;
-constexpr int32_t walk_spread(int precision, bool step)
+constexpr int32_t walk_spread(int precision, bool step, int64_t n)
 {
-    return (int32_t)(kSpreadSamples * (precision == MD_MIXED ? (step ? 8.0 : 1.4) : (step ? 1.25 : 1.0)));
+    if (precision == MD_MIXED) return (int32_t)(kSpreadSamples * (step ? 8.0 : 1.4));
+    return (int32_t)(kSpreadSamples * (!step ? 1.0 : (n < 786432 ? 0.95 : 1.25)));
 }
 
 // md_pairlist.hip
